@@ -46,6 +46,8 @@ static unsigned char* scratch_of(int dev) {
 }
 
 tfhe_status plan_build(tfhe_ntt_plan_s* p);
+// (plan.cpp) appends the second inverse pass's twist of a limb, times a constant
+void scaled_twist(const tfhe_ntt_plan_s* p, uint32_t limb, uint32_t scale, std::vector<uint2>& out);
 void plan_free(tfhe_ntt_plan_s* p);
 
 static uint32_t mulm(uint32_t a, uint32_t b, uint32_t q) { return (uint32_t)((uint64_t)a * b % q); }
@@ -67,6 +69,13 @@ static hipError_t ntt_units(const tfhe_ntt_plan_s* p, const std::vector<NttUnit>
 // separate kernels (2).
 static bool fused_inner(const tfhe_ckks_ctx_s* c) {
   return c->plan->algo == TFHE_NTT_FOURSTEP_MFMA && c->plan->ks_inner != 2;
+}
+
+// Whether inverse transforms that feed a conversion or a broadcast input
+// write quad-tiled results: where their second pass is the two-pass kernel's
+// and natural order would be read in 16- or 32-byte pieces (N >= 2^15).
+static bool quad_tiled(const tfhe_ntt_plan_s* p) {
+  return p->algo == TFHE_NTT_FOURSTEP_MFMA && p->log_n >= 15 && p->fs_passes != 1;
 }
 
 // Workspace of one key-switching batch: its own regions (byte offsets from
@@ -165,7 +174,8 @@ static hipError_t key_switch_multi(const tfhe_ckks_ctx_s* c, const KsJob* jobs, 
                                    unsigned char* nws, hipStream_t s) {
   if (nj > (uint32_t)kMaxIpGroups) return hipErrorInvalidValue;
   const tfhe_ntt_plan_s* p = c->plan;
-  const bool fused = fused_inner(c);
+  const bool four_step = p->algo == TFHE_NTT_FOURSTEP_MFMA;  // ModDown converts in the final transforms' first pass
+  const bool fused = fused_inner(c), tiled = quad_tiled(p);
   struct Ptrs {
     uint32_t *x, *up, *acc, *tp, *conv, *inter;
     uint64_t plane;
@@ -186,14 +196,30 @@ static hipError_t key_switch_multi(const tfhe_ckks_ctx_s* c, const KsJob* jobs, 
   hipError_t e;
   // INTT of the inputs (coefficient domain for the basis conversion)
   std::vector<NttUnit> units;
-  for (uint32_t g = 0; g < nj; ++g)
-    units.push_back(NttUnit{p, true, jobs[g].d, w[g].x, 0, jobs[g].level, jobs[g].batch});
+  for (uint32_t g = 0; g < nj; ++g) {
+    if (!fused) {
+      units.push_back(NttUnit{p, true, jobs[g].d, w[g].x, 0, jobs[g].level, jobs[g].batch});
+      continue;
+    }
+    // per digit, times the constants of its conversion
+    for (uint32_t j = 0; j < w[g].digits; ++j) {
+      const uint32_t d0 = c->alpha * j, nd = std::min(c->alpha, jobs[g].level - d0);
+      NttUnit u{p, true, jobs[g].d + d0 * w[g].plane, w[g].x + d0 * w[g].plane, d0, nd, jobs[g].batch};
+      u.twist = c->d_up_tw + (size_t)(d0 + nd - 1) * c->alpha * 256;
+      u.out_tiled = tiled;
+      units.push_back(u);
+    }
+  }
   if ((e = ntt_units(p, units, nws, s)) != hipSuccess) return e;
-  // Dcomp + ModUp of every digit, then one fused NTT of all converted limbs:
-  // the q-limbs before and after the digit, and the p-limbs.  Fused: the
-  // transforms' first pass writes digit j's intermediate of position pos at
-  // inter + (j ext + pos) plane; ip_run finishes them.
+  // Dcomp + ModUp of every digit and the NTT of the converted limbs.  Fused
+  // inner product: one unit per digit, converted in the transforms' first
+  // pass, which writes digit j's intermediate of position pos at
+  // inter + (j ext + pos) plane; ip_run finishes them.  Else one conversion
+  // launch and one fused NTT of the q-limbs before and after the digit and
+  // the p-limbs.
   units.clear();
+  std::vector<ConvSource> src;  // of the units (which point to it)
+  src.reserve((size_t)nj * (c->dnum + 1));
   ConvQueue cq;  // the matrix-core conversions, launched together
   cq.tabs = conv_tabs(c);
   for (uint32_t g = 0; g < nj; ++g) {
@@ -202,6 +228,14 @@ static hipError_t key_switch_multi(const tfhe_ckks_ctx_s* c, const KsJob* jobs, 
     for (uint32_t j = 0; j < w[g].digits; ++j) {
       const uint32_t d0 = c->alpha * j, nd = std::min(c->alpha, level - d0);
       const uint32_t key_idx = d0 + nd - 1;
+      if (fused) {
+        src.push_back(ConvSource{c->d_up_cv + (size_t)key_idx * (c->L + c->K), nd, d0, nd, level, c->L, tiled});
+        NttUnit u{p, false, w[g].x + d0 * plane, w[g].inter + (uint64_t)j * ext * plane, 0, ext - nd, batch};
+        u.pass1_only = u.in_bcast = true;
+        u.conv = &src.back();
+        units.push_back(u);
+        continue;
+      }
       uint32_t* upj = w[g].up + (uint64_t)j * ext * plane;
       if (mfma_conv)
         modup_mfma(w[g].x, upj, key_idx, d0, nd, level, c->K, plane, cq);
@@ -209,11 +243,9 @@ static hipError_t key_switch_multi(const tfhe_ckks_ctx_s* c, const KsJob* jobs, 
                                  c->d_up_conv + (size_t)key_idx * (c->L + c->K) * kMaxAlpha, d0, nd, level,
                                  c->L, c->K, batch, c->n, s)) != hipSuccess)
         return e;
-      uint32_t* outj = fused ? w[g].inter + (uint64_t)j * ext * plane : upj;
       auto unit = [&](uint32_t pos, uint32_t limb_begin, uint32_t count) {
-        NttUnit u{p, false, upj + (uint64_t)pos * plane, outj + (uint64_t)pos * plane, limb_begin, count, batch};
-        u.pass1_only = fused;
-        units.push_back(u);
+        units.push_back(
+            NttUnit{p, false, upj + (uint64_t)pos * plane, upj + (uint64_t)pos * plane, limb_begin, count, batch});
       };
       if (d0) unit(0, 0, d0);
       if (level > d0 + nd) unit(d0 + nd, d0 + nd, level - d0 - nd);
@@ -238,11 +270,17 @@ static hipError_t key_switch_multi(const tfhe_ckks_ctx_s* c, const KsJob* jobs, 
     const uint64_t plane = w[g].plane;
     const uint32_t level = jobs[g].level, batch = jobs[g].batch;
     uint32_t* a1 = w[g].acc + (uint64_t)w[g].ext * plane;
-    units.push_back(NttUnit{p, true, w[g].acc + (uint64_t)level * plane, w[g].tp, c->L, c->K, batch});
-    units.push_back(NttUnit{p, true, a1 + (uint64_t)level * plane, w[g].tp + (uint64_t)c->K * plane, c->L, c->K, batch});
+    NttUnit u0{p, true, w[g].acc + (uint64_t)level * plane, w[g].tp, c->L, c->K, batch};
+    NttUnit u1{p, true, a1 + (uint64_t)level * plane, w[g].tp + (uint64_t)c->K * plane, c->L, c->K, batch};
+    if (four_step) {
+      u0.twist = u1.twist = c->d_dn_tw;  // times the constants of the conversion
+      u0.out_tiled = u1.out_tiled = tiled;
+    }
+    units.push_back(u0);
+    units.push_back(u1);
   }
   if ((e = ntt_units(p, units, nws, s)) != hipSuccess) return e;
-  for (uint32_t g = 0; g < nj; ++g) {
+  for (uint32_t g = 0; g < nj && !four_step; ++g) {
     const uint64_t plane = w[g].plane;
     const uint32_t level = jobs[g].level;
     for (int comp = 0; comp < 2; ++comp) {
@@ -262,11 +300,15 @@ static hipError_t key_switch_multi(const tfhe_ckks_ctx_s* c, const KsJob* jobs, 
     const uint64_t plane = w[g].plane;
     uint32_t* conv1 = w[g].conv + (uint64_t)j.level * plane;
     uint32_t* a1 = w[g].acc + (uint64_t)w[g].ext * plane;
-    if (p->algo == TFHE_NTT_FOURSTEP_MFMA) {
-      // the transform's second pass finishes ModDown in its store epilogue:
+    if (four_step) {
+      // the transform's first pass converts the special limbs, its second
+      // pass finishes ModDown in its store epilogue:
       // out (+)= (acc - NTT(conv)) P^{-1}
-      NttUnit u0{p, false, w[g].conv, j.out0, 0, j.level, j.batch};
-      NttUnit u1{p, false, conv1, j.out1, 0, j.level, j.batch};
+      NttUnit u0{p, false, w[g].tp, j.out0, 0, j.level, j.batch};
+      NttUnit u1{p, false, w[g].tp + (uint64_t)c->K * plane, j.out1, 0, j.level, j.batch};
+      src.push_back(ConvSource{c->d_dn_cv, c->K, j.level, 0, j.level, c->L, tiled});
+      u0.in_bcast = u1.in_bcast = true;
+      u0.conv = u1.conv = &src.back();
       u0.acc = w[g].acc;
       u1.acc = a1;
       u0.epi_mult = u1.epi_mult = c->d_dn_pinv;
@@ -280,7 +322,7 @@ static hipError_t key_switch_multi(const tfhe_ckks_ctx_s* c, const KsJob* jobs, 
     }
   }
   if ((e = ntt_units(p, units, nws, s)) != hipSuccess) return e;
-  if (p->algo == TFHE_NTT_FOURSTEP_MFMA) return hipSuccess;
+  if (four_step) return hipSuccess;
   for (uint32_t g = 0; g < nj; ++g) {
     const KsJob& j = jobs[g];
     const uint64_t plane = w[g].plane;
@@ -426,10 +468,10 @@ static hipError_t rescale(const tfhe_ckks_ctx_s* c, const uint32_t* ct, uint32_t
   void* nws = ws + lay.ntt;
   hipError_t e;
   // INTT of both components' top limb
-  if ((e = ntt_units(p, {NttUnit{p, true, ct + (uint64_t)top * plane, t, top, 1, batch},
-                         NttUnit{p, true, ct + (uint64_t)(level + top) * plane, t + plane, top, 1, batch}},
-                     nws, s)) != hipSuccess)
-    return e;
+  NttUnit i0{p, true, ct + (uint64_t)top * plane, t, top, 1, batch};
+  NttUnit i1{p, true, ct + (uint64_t)(level + top) * plane, t + plane, top, 1, batch};
+  i0.out_tiled = i1.out_tiled = quad_tiled(p);
+  if ((e = ntt_units(p, {i0, i1}, nws, s)) != hipSuccess) return e;
   if (p->algo == TFHE_NTT_FOURSTEP_MFMA) {
     // NTT of the top limb's coefficients modulo every remaining limb (each
     // limb's first pass reads the same plane of t, whose values lie below
@@ -437,6 +479,7 @@ static hipError_t rescale(const tfhe_ckks_ctx_s* c, const uint32_t* ct, uint32_t
     NttUnit u0{p, false, t, out, 0, top, batch};
     NttUnit u1{p, false, t + plane, out + (uint64_t)top * plane, 0, top, batch};
     u0.in_bcast = u1.in_bcast = true;
+    u0.in_tiled = u1.in_tiled = quad_tiled(p);
     u0.acc = ct;
     u1.acc = ct + (uint64_t)level * plane;
     u0.epi_mult = u1.epi_mult = c->d_rs_qinv + (size_t)top * c->L;
@@ -463,6 +506,7 @@ static hipError_t upload(T** dst, const std::vector<T>& src, std::vector<void*>&
   hipError_t e = hipMalloc((void**)dst, sizeof(T) * std::max<size_t>(src.size(), 1));
   if (e != hipSuccess) return e;
   owned.push_back(*dst);
+  if (src.empty()) return hipSuccess;
   return hipMemcpy(*dst, src.data(), sizeof(T) * src.size(), hipMemcpyHostToDevice);
 }
 
@@ -547,6 +591,36 @@ static tfhe_status ctx_build(tfhe_ckks_ctx_s* c) {
     for (uint32_t k = 0; k < K; ++k) sum = (uint32_t)(((uint64_t)sum + dconv[(size_t)i * kMaxK + k].x) % m[i]);
     dn_k[i] = mulm(sum, k30(m[i]), m[i]);
   }
+  // conversions fused with the first pass: C 2^32 in [-m/2, m/2)
+  auto target = [&](const uint2* C, uint32_t n, uint32_t mt) {
+    CvTarget t{};
+    t.q = mt;
+    t.qneg = make_modconst(mt).qneg;
+    uint32_t sum = 0;
+    for (uint32_t r = 0; r < n; ++r) {
+      const uint32_t w = mulm(C[r].x, (uint32_t)((1ull << 32) % mt), mt);
+      t.c[r] = w > mt / 2 ? (int32_t)(w - mt) : (int32_t)w;
+      sum = (uint32_t)(((uint64_t)sum + w) % mt);
+    }
+    t.init = ((uint64_t)mt << 32) + mulm(sum, k30(mt), mt);
+    return t;
+  };
+  std::vector<CvTarget> up_cv((size_t)L * (L + K)), dn_cv(L);
+  for (uint32_t e = 1; e <= L; ++e)
+    for (uint32_t t = 0; t < L + K; ++t)
+      up_cv[(size_t)(e - 1) * (L + K) + t] =
+          target(&up_conv[((size_t)(e - 1) * (L + K) + t) * kMaxAlpha], e - A * ((e - 1) / A), m[t]);
+  for (uint32_t i = 0; i < L; ++i) dn_cv[i] = target(&dconv[(size_t)i * kMaxK], K, m[i]);
+  // their inputs' constants, folded into the inverse transforms' last twist
+  std::vector<uint2> up_tw, dn_tw;
+  if (c->plan->has_mfma) {
+    for (uint32_t e = 1; e <= L; ++e)
+      for (uint32_t r = 0; r < A; ++r) {
+        const uint32_t i = A * ((e - 1) / A) + r;
+        scaled_twist(c->plan, i, i < e ? up_inv[(size_t)(e - 1) * kMaxAlpha + r].x : 1, up_tw);
+      }
+    for (uint32_t k = 0; k < K; ++k) scaled_twist(c->plan, L + k, invp[k].x, dn_tw);
+  }
   std::vector<uint2> rsq((size_t)L * L, make_uint2(0, 0));
   for (uint32_t t = 1; t < L; ++t)
     for (uint32_t i = 0; i < t; ++i)
@@ -555,6 +629,10 @@ static tfhe_status ctx_build(tfhe_ckks_ctx_s* c) {
   if ((e = upload(&c->d_rs_qinv, rsq, c->owned)) != hipSuccess ||
       (e = upload(&c->d_up_mfma, up_mfma, c->owned)) != hipSuccess ||
       (e = upload(&c->d_dn_mfma, dn_mfma, c->owned)) != hipSuccess ||
+      (e = upload(&c->d_up_cv, up_cv, c->owned)) != hipSuccess ||
+      (e = upload(&c->d_dn_cv, dn_cv, c->owned)) != hipSuccess ||
+      (e = upload(&c->d_up_tw, up_tw, c->owned)) != hipSuccess ||
+      (e = upload(&c->d_dn_tw, dn_tw, c->owned)) != hipSuccess ||
       (e = upload(&c->d_up_k, up_k, c->owned)) != hipSuccess ||
       (e = upload(&c->d_dn_k, dn_k, c->owned)) != hipSuccess ||
       (e = upload(&c->d_up_inv, up_inv, c->owned)) != hipSuccess ||

@@ -25,6 +25,12 @@ struct CkksCtxImpl {
   // their offset constants 2^30 sum_r C[t][r] mod m_t
   uint32_t* d_up_k = nullptr;     // [L (digit end - 1)][L+K (target)]
   uint32_t* d_dn_k = nullptr;     // [L (target)]
+  // Constants of the conversions fused with the transforms' first pass:
+  CvTarget* d_up_cv = nullptr;    // [L (digit end - 1)][L+K (target)]
+  CvTarget* d_dn_cv = nullptr;    // [L (target)]
+  // ... and their inputs' constants times the second inverse pass's twist:
+  uint2* d_up_tw = nullptr;       // [L (digit end - 1)][alpha][64][4]
+  uint2* d_dn_tw = nullptr;       // [K][64][4]
   std::vector<void*> owned;
 };
 

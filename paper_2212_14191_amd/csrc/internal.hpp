@@ -46,20 +46,24 @@ struct CoPass {
 };
 
 // Tables of the one-pass four-step kernel (N = 2^12..2^15) for one limb and
-// direction; its first pass uses the two-pass kernel's pass-1 tables.
+// direction; its first pass uses the two-pass kernel's pass-1 tables.  The
+// post-twist factors also serve the conversion-fused first pass (forward,
+// N = 2^12..2^16), whose waves each take one step's columns.
 //   p2       second pass.  Forward (256-point): level B's twiddles unscaled
 //            and the twist carrying 2^64, so opB equals opA (the 16-point DFT
 //            matrix is symmetric).  Inverse (N1-point): opA with the level-A
 //            index u = g + 4c for lane (i, g), dword c, instead of 4g + c.
-//   post_b   [lane][j][set] first-pass post-twist, the factor fixed per lane:
-//            P(4m + set, out) (times 2^32 after a matrix-core level B), Shoup
+//   post_b   [set][j / 2][lane][j % 2] first-pass post-twist, the factor fixed
+//            per lane: P(4m + set, out) (times 2^32 after a matrix-core level
+//            B), Shoup; a lane's 16 bytes lie next to the next lane's, so that
+//            LDS copies are read without bank conflicts
 //   post_a   [step][lane][j] the factor of a step whose first column quad is
 //            Q0 = step * 16 / r: P(4 Q0 + 4m, out) / P(4m, out), times 2^32
 //            (Montgomery form); (m, out) as lane / register j hold them.
 struct OnePassTables {
   PassTables p2;
-  uint2 post_b[64][4][4];
-  uint32_t post_a[32][64][4];
+  uint2 post_b[4][2][64][2];
+  uint32_t post_a[64][64][4];
 };
 
 // Device-side description of one limb for the four-step kernels.
@@ -70,7 +74,7 @@ struct FourStepLimb {
   const CoPass* co1;        // vector-ALU variant (N = 2^16 only): pass matrices
   const CoPass* co2;
   const uint2* co_post;     // [256 columns][256 outputs]: post-twist of pass 1
-  const OnePassTables* op;  // one-pass kernel (N = 2^12..2^15), else null
+  const OnePassTables* op;  // one-pass kernel (its p2: N = 2^12..2^15)
   uint32_t q, qneg;         // modulus and -q^{-1} mod 2^32
 };
 
@@ -94,7 +98,9 @@ struct tfhe_plan_impl {
   uint2* d_ninv = nullptr;        // [n_limbs] {N^{-1}, companion}
   FourStepLimb* d_fs_fwd = nullptr;  // [n_limbs]
   FourStepLimb* d_fs_inv = nullptr;  // [n_limbs]
-  void* d_fs_blob = nullptr;          // owns all four-step tables
+  void* d_fs_blob = nullptr;          // owns all four-step tables: limb l, direction d at (2 l + d) fs_limb_bytes
+  size_t fs_limb_bytes = 0;           // (pass 1's PassTables at 0, OnePassTables at fs_op_off)
+  size_t fs_op_off = 0;
   std::vector<void*> owned;
 };
 
@@ -103,6 +109,26 @@ struct tfhe_plan_impl {
 struct tfhe_ntt_plan_s : tfhe::tfhe_plan_impl {};
 
 namespace tfhe {
+
+// Constants of one target modulus m of a basis conversion fused with a
+// transform (ntt_convpass.hip): c[r] the representative of C[r] 2^32 mod m in
+// [-m/2, m/2), init = m 2^32 + (2^30 sum_r c[r] mod m).
+struct CvTarget {
+  int32_t c[8];
+  uint64_t init;
+  uint32_t q, qneg;
+};
+// The basis conversion whose results a forward transform takes as its input
+// (NttUnit::conv): x_t = sum_r y_r C[t][r] mod m_t from nin <= 8 planes of
+// residues y_r (already times the inputs' constants: NttUnit::twist).  Target
+// u is extended-basis position pos = u, or u + nd from the digit's first limb
+// d0 on (its own nd limbs are skipped); position pos is plan limb pos below
+// `level`, L + pos - level above.
+struct ConvSource {
+  const CvTarget* tgt;  // [plan limb]
+  uint32_t nin, d0, nd, level, L;
+  bool tiled;           // the inputs are quad-tiled (NttUnit::out_tiled)
+};
 
 // ---- operation-level batching: one fused launch over many transforms
 // A transform unit: `batch` polynomials of limbs [limb_begin, +limb_count) of
@@ -129,6 +155,22 @@ struct NttUnit {
   // limb's modulus), i.e. the transform of that integer polynomial modulo
   // each of the unit's limbs
   bool in_bcast = false;
+  // With in_bcast: the limbs' inputs are the results of this conversion of
+  // the nin planes at `in` ([nin][batch][N]); limb_count counts its targets
+  // (limb_begin 0), and with pass1_only target u's tiled intermediate goes
+  // to position pos of `out` ([level + K][batch][N]).
+  const ConvSource* conv = nullptr;
+  // With in_bcast and no conversion: the input plane is quad-tiled
+  bool in_tiled = false;
+  // Inverse four-step transforms of N >= 2^15 only (two passes): the results
+  // are written quad by quad, coefficient n = 256 n1 + n2 of a polynomial at
+  // ((n2 / 4) N1 + n1) 4 + n2 % 4 (N1 = N / 256), as a conversion or broadcast
+  // input reads them
+  bool out_tiled = false;
+  // Inverse four-step transforms only: the second pass's twist of each limb
+  // ([limb_count][64][4]), the plan's times a constant of the limb: the
+  // results come out times that constant.
+  const uint2* twist = nullptr;
 };
 // Runs every unit with the four-step algorithm (all units need has_mfma) or
 // the butterfly; ws must hold the sum of the units' workspaces.
@@ -172,7 +214,8 @@ struct GaloisSet {
 // ---- per-kernel event timing (timing.cpp)
 enum KernelId {
   K_FS_PASS1 = 0, K_FS_PASS2, K_BF_SINGLE, K_BF_COLS, K_BF_ROWS, K_EW, K_TENSOR, K_MODUP,
-  K_INNER, K_MD_CONV, K_MD_FINAL, K_FROB, K_RS_BCAST, K_RS_FINAL, K_CO_PASS1, K_CO_PASS2, K_OP, K_IP
+  K_INNER, K_MD_CONV, K_MD_FINAL, K_FROB, K_RS_BCAST, K_RS_FINAL, K_CO_PASS1, K_CO_PASS2, K_OP, K_IP,
+  K_CONV_PASS1
 };
 // Resident workgroups per CU of a kernel, queried once per process: the
 // dispatcher's workers may race to fill the cache; they store one value.

@@ -56,32 +56,6 @@
 namespace tfhe {
 namespace {
 
-// Geometry of a pass with P = 16 kR points.  A work item is P rows x W
-// vectors (columns) of one polynomial, 1024 words per wave; each wave
-// transforms four sets of vectors per item.  Its LDS tile is a sequence of
-// 1 KiB slabs; slab k holds rows Rs k .. Rs k + Rs - 1 of every column of the
-// item, slot L (16 bytes) row Rs k + L % Rs, columns 4 (L / Rs) .. + 3 (a
-// "quad"), so one direct-to-LDS load covers Rs rows x W columns.  Narrow
-// items (W = 16 for kR = 16) use 4 waves and Rs = 16: 64-byte row segments.
-// Wide items (kR = 16 with at least 32 columns) use 8 waves and Rs = 8, so
-// every load and store moves whole 128-byte lines.  For kR < 16, Rs = kR and
-// W = 256 / kR >= 32.  Slabs are padded where 16 lanes of an LDS access
-// would otherwise hit the same banks in several slabs.
-template <bool kFirst, int kR, bool kWide>
-struct Geo {
-  static constexpr int waves = kWide ? 8 : 4;
-  static constexpr int threads = 64 * waves;
-  static constexpr int item = 1024 * waves;      // words per work item
-  static constexpr int slabs = item / 256;
-  static constexpr int P = 16 * kR;
-  static constexpr int W = item / P;             // vectors per item
-  static constexpr int Mt = 16 / kR;             // vectors per MFMA tile (quads per wave)
-  static constexpr int Rs = kWide ? 8 : kR;      // rows per slab
-  static constexpr int pitch = kWide ? 256 + 32 : (kFirst || kR == 16) ? 256 : 256 + 4 * kR;
-  static constexpr int tile = slabs * pitch;
-  static_assert(!kWide || kR == 16, "wide items are for the 256-point stage");
-};
-
 // Work distribution.  The grid is a multiple of 16.  Workgroup w belongs to
 // group w / 16, which owns a contiguous range of polynomials; within the
 // group, slot j = 2 (c % 8) + c / 8 of workgroup c = w % 16 selects its item
@@ -94,46 +68,15 @@ struct Geo {
 struct Walk {
   uint32_t blk, p, step, p_end;
 };
-__device__ __forceinline__ Walk make_walk(uint32_t total_polys, uint32_t ipp_log) {
-  const uint32_t groups = gridDim.x / 16, a = blockIdx.x / 16, c = blockIdx.x % 16;
+__device__ __forceinline__ Walk make_walk(const FsTable& t) {
+  const uint32_t a = blockIdx.x / 16, c = blockIdx.x % 16, ipp_log = t.ipp_log;
   const uint32_t j = 2 * (c % 8) + c / 8;
   Walk w;
   w.blk = j & ((1u << ipp_log) - 1);
   w.step = 16u >> ipp_log;
-  w.p = (uint32_t)((uint64_t)a * total_polys / groups) + (j >> ipp_log);
-  w.p_end = (uint32_t)((uint64_t)(a + 1) * total_polys / groups);
+  w.p = a * t.share + min(a, t.extra) + (j >> ipp_log);
+  w.p_end = (a + 1) * t.share + min(a + 1, t.extra);
   return w;
-}
-
-// Each wave loads slabs 4 wave .. 4 wave + 3 of an item: one 16-byte
-// direct-to-LDS load per lane per slab (streaming hint: every byte is read
-// once; a broadcast input, read once per limb, is loaded without it, which
-// measured 3 % faster for RESCALE); lane L's bytes land at the slab base +
-// 16 L.  Issued as inline assembly so that the compiler does not serialise
-// later LDS reads on these loads: the pipeline waits for them explicitly
-// (wait_item) before a barrier.
-template <int kPitch>
-__device__ __forceinline__ void issue_tile(const uint32_t* src, const uint32_t* off, uint32_t* stage,
-                                           int wave, bool cached = false) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const uint32_t* g = src + off[j];
-    const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_void_t*)(stage + (4 * wave + j) * kPitch);
-    if (cached)
-      asm volatile(
-          "s_mov_b32 m0, %0\n\t"
-          "global_load_lds_dwordx4 %1, off"
-          :
-          : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(g)
-          : "memory", "m0");
-    else
-      asm volatile(
-          "s_mov_b32 m0, %0\n\t"
-          "global_load_lds_dwordx4 %1, off nt"
-          :
-          : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(g)
-          : "memory", "m0");
-  }
 }
 
 // Wait until this wave's loads of the current item have landed.  Vector
@@ -163,7 +106,8 @@ __device__ __forceinline__ void wait_item(uint32_t n, bool has_next) {
 }
 
 template <bool kFirst, int kR, bool kWide, bool kEpi = false, int kRing = 3>
-__global__ void __launch_bounds__(kWide ? 512 : 256, (kWide || kEpi) ? 2 : 3)
+__global__ void __launch_bounds__(kWide ? 512 : 256) __attribute__((
+    amdgpu_waves_per_eu(kWide || kEpi ? 2 : 3, kWide ? 2 : 8)))
 fs_pass(const FsTable tab) {
   static_assert(!kEpi || (!kFirst && kR == 16), "the epilogue belongs to the forward second pass");
   using G = Geo<kFirst, kR, kWide>;
@@ -176,7 +120,7 @@ fs_pass(const FsTable tab) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint32_t* const gather = kGather ? ring + kRing * G::tile + wave * 1024 : ring;
   const int i16 = lane & 15, g = lane >> 4;
-  const Walk walk = make_walk(tab.total, tab.ipp_log);
+  const Walk walk = make_walk(tab);
   if (walk.p >= walk.p_end) return;
   const uint32_t S = tab.cols, c0 = walk.blk * G::W;
 
@@ -201,20 +145,24 @@ fs_pass(const FsTable tab) {
       st_off[j] = natural;
     }
   }
+  // second pass: this lane's stores in quad-tiled order
+  uint32_t st_tiled[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    st_tiled[j] = (((c0 >> 2) + lane / G::Rs) * G::P + G::Rs * (4 * wave + j) + lane % G::Rs) * 4;
 
-  uint32_t kf = 0, kc = 0;  // running unit indices of the load and compute walks
+  // running unit indices of the load and compute walks
+  uint32_t kf = find_unit(tab.begin, tab.count, walk.p), kc = kf;
   auto issue = [&](uint32_t p, int stage) {
     const Item it = locate(tab, p, kf);
-    issue_tile<G::pitch>(tab.u[it.unit].in + it.in_base, ld_off, ring + stage * G::tile, wave,
-                         kFirst && tab.u[it.unit].in_bcast);
+    issue_tile<G::pitch>(tab.u[it.unit].in + it.poly_base, ld_off, ring + stage * G::tile, wave);
   };
 #pragma unroll
   for (int j = 0; j < kRing - 1; ++j)
     if (walk.p + j * walk.step < walk.p_end) issue(walk.p + j * walk.step, j);
 
-  const FourStepLimb* cur_limb = nullptr;
-  uint32_t q = 0, qneg = 0, nq = 0;
-  uint64_t cq = 0;  // 0x80808080 - q mod 2^32 (zero-extended), the twist's digit offset
+  const void* cur = nullptr;  // whose tables are loaded: the limb's, with the unit's twist if it has one
+  Red R{};
   v4i opA[4], opB[4];
   uint2 tw[4];
   uint2 pt[4][4];  // pass 1: post-twist per set and register
@@ -226,20 +174,19 @@ fs_pass(const FsTable tab) {
   for (uint32_t p = walk.p; p < walk.p_end; p += walk.step, ++n, st = (st + 1 == kRing) ? 0 : st + 1) {
     const Item it = locate(tab, p, kc);
     const FourStepLimb* limb = tab.u[it.unit].limbs + it.limb;
-    if (limb != cur_limb) {
+    const uint2* const twist = kFirst ? nullptr : tab.u[it.unit].twist;
+    const void* const key = twist ? (const void*)(twist + it.limb * 256) : limb;
+    if (key != cur) {
       // rare (a few times per workgroup): completed here, so that the
       // steady-state path carries no wait on these loads
-      const FourStepLimb L = *limb;
-      const PassTables* P = kFirst ? L.pass1 : L.pass2;
-      q = L.q;
-      qneg = L.qneg;
-      nq = 0u - q;
-      cq = (uint32_t)(0x80808080u - q);
+      const auto* L = (const_as FourStepLimb*)limb;
+      const PassTables* P = kFirst ? L->pass1 : L->pass2;
+      R = make_red(L->q, L->qneg);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         opA[j] = *(const v4i*)&P->opA[j][lane][0];
         if (kR == 16) opB[j] = *(const v4i*)&P->opB[j][lane][0];
-        tw[j] = P->twist[lane][j];
+        tw[j] = (twist ? twist + it.limb * 256 : &P->twist[0][0])[lane * 4 + j];
         if (kR < 16) {
           lb[j] = P->lb[j];
           int m, t;
@@ -254,13 +201,15 @@ fs_pass(const FsTable tab) {
       if (kFirst) {
 #pragma unroll
         for (int sg = 0; sg < 4; ++sg) {
-          const uint2* pp = L.post1 + ((size_t)(c0 + 4 * wave * G::Mt + sg) * 64 + lane) * 4;
+          const uint2* pp = L->post1 + ((size_t)(c0 + 4 * wave * G::Mt + sg) * 64 + lane) * 4;
 #pragma unroll
           for (int j = 0; j < 4; ++j) pt[sg][j] = pp[j];
         }
       }
-      wait_vmcnt<0>();
-      cur_limb = limb;
+      // the builtin (unlike an asm wait) tells the compiler these registers
+      // are ready: it would otherwise wait at their uses for every item
+      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+      cur = key;
     }
     const bool has_next = p + walk.step < walk.p_end;
     wait_item<kRing, kFirst && !kWide ? 16 : 4, kEpi ? 8 : 0>(n, has_next);
@@ -295,17 +244,28 @@ fs_pass(const FsTable tab) {
 
     uint32_t* const out = tab.u[it.unit].out + it.poly_base;
     uint4 res[4];  // pass 2: res[j] = the four sets' outputs of register j
-    // The digit window needs a correction only for q > 0x7F7F7F7F; q is
-    // uniform, so the item body is instantiated for both cases.
-    auto body = [&](auto big_q) {
-      constexpr bool kBigQ = decltype(big_q)::value;
+    const uint32_t q = R.q;
+    if (kFirst) {
+      // only moduli above 0x7F7F7F7F (uniform) need the window's correction
+      if (q > 0x7F7F7F7Fu) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          rows[c] = make_uint4(residue_digits_big(rows[c].x, q), residue_digits_big(rows[c].y, q),
+                               residue_digits_big(rows[c].z, q), residue_digits_big(rows[c].w, q));
+      } else {
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          rows[c] = make_uint4(residue_digits(rows[c].x), residue_digits(rows[c].y), residue_digits(rows[c].z),
+                               residue_digits(rows[c].w));
+      }
+    }
+    {
 #pragma unroll
       for (int sg = 0; sg < 4; ++sg) {
         v4i x;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-          const uint32_t w = sg == 0 ? rows[c].x : sg == 1 ? rows[c].y : sg == 2 ? rows[c].z : rows[c].w;
-          x[c] = kFirst ? (int)balanced_digits(kBigQ ? to_window(w, q) : (int32_t)w) : (int)w;
+          x[c] = (int)(sg == 0 ? rows[c].x : sg == 1 ? rows[c].y : sg == 2 ? rows[c].z : rows[c].w);
         }
         const v4i bias = {(int)q, (int)q, (int)q, (int)q};
         const v4i zero = {0, 0, 0, 0};
@@ -318,17 +278,17 @@ fs_pass(const FsTable tab) {
           v4i z;
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            z[j] = (int)twist_digits<kBigQ>(fuse_redc(a0[j], a1[j], a2[j], a3[j], q, qneg), tw[j], q, nq, cq);
+            z[j] = (int)twist_digits(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw[j], R);
           const v4i b0 = mfma(opB[0], z, bias);
           const v4i b1 = mfma(opB[1], z, zero);
           const v4i b2 = mfma(opB[2], z, bias);
           const v4i b3 = mfma(opB[3], z, zero);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) y[j] = fuse_redc(b0[j], b1[j], b2[j], b3[j], q, qneg);
+          for (int j = 0; j < 4; ++j) y[j] = fuse_redc(b0[j], b1[j], b2[j], b3[j], R);
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            y[j] = reduce_once(mul_shoup_lazy(fuse_redc(a0[j], a1[j], a2[j], a3[j], q, qneg), tw[j].x, tw[j].y, q), q);
+            y[j] = reduce_once(mul_shoup_lazy(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw[j].x, tw[j].y, q), q);
           level_b<kR>(y, lb, rj, g, q);
         }
         if (kGather) {
@@ -337,10 +297,10 @@ fs_pass(const FsTable tab) {
           // four lane groups write disjoint banks
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            gather[(4 * g + j) * 64 + 16 * (sg ^ g) + i16] = twist_digits<kBigQ>(y[j], pt[sg][j], q, nq, cq);
+            gather[(4 * g + j) * 64 + 16 * (sg ^ g) + i16] = twist_digits(y[j], pt[sg][j], R);
         } else if (kFirst) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) out[st_off[j] + 16 * sg] = twist_digits<kBigQ>(y[j], pt[sg][j], q, nq, cq);
+          for (int j = 0; j < 4; ++j) out[st_off[j] + 16 * sg] = twist_digits(y[j], pt[sg][j], R);
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
@@ -352,14 +312,7 @@ fs_pass(const FsTable tab) {
           }
         }
       }
-    };
-    // (the narrow first pass of the 256-point stage keeps one body: two
-    // would not fit its register budget without spilling).  A broadcast
-    // input (below 2^31, not reduced by this limb's modulus) takes the body
-    // that maps its values into the digit window.
-    constexpr bool kDual = !(kFirst && kR == 16 && !kWide);
-    if (!kDual || q > 0x7F7F7F7Fu || (kFirst && tab.u[it.unit].in_bcast)) body(std::true_type{});
-    else body(std::false_type{});
+    }
 
     if (kGather) {
       // this wave's runs t = 4 j + g, words 4 i16 .. 4 i16 + 3 (unswizzled).
@@ -391,7 +344,9 @@ fs_pass(const FsTable tab) {
         if (issued) wait_vmcnt<4>();
         else wait_vmcnt<0>();
         const FsUnit& U = tab.u[it.unit];
-        const uint2 m = U.mult[it.limb];
+        // (a scalar load: a vector load here would wait for the ring as well)
+        const auto* mp = (const_as uint32_t*)(U.mult + it.limb);
+        const uint2 m = make_uint2(mp[0], mp[1]);
         const bool add = U.accumulate != 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -410,9 +365,11 @@ fs_pass(const FsTable tab) {
           __builtin_nontemporal_store(*(const v4u*)&r, (v4u*)(out + st_off[j]));
         }
       } else {
+        const bool tiled = tab.u[it.unit].out_tiled != 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          __builtin_nontemporal_store(*(const v4u*)(tile + (4 * wave + j) * G::pitch + lane * 4), (v4u*)(out + st_off[j]));
+          __builtin_nontemporal_store(*(const v4u*)(tile + (4 * wave + j) * G::pitch + lane * 4),
+                                      (v4u*)(out + (tiled ? st_tiled[j] : st_off[j])));
       }
     }
   }
@@ -428,13 +385,18 @@ uint32_t occupancy() {
 // Persistent grid: a multiple of 16 workgroups, no more than the items need.
 template <bool kFirst, int kR, bool kWide, bool kEpi, int kRing>
 uint32_t grid_size(const tfhe_ntt_plan_s* p, uint32_t items) {
-  // default: the resident count; twice that for the wide kernels (one or
-  // two resident workgroups per CU), whose tail balances better with the
-  // second half of the grid scheduled as the first half drains (measured)
-  const uint32_t w =
-      p->fs_wg_per_cu ? p->fs_wg_per_cu : occupancy<kFirst, kR, kWide, kEpi, kRing>() * (kWide ? 2 : 1);
+  // default: the resident count; for the wide kernels (one resident
+  // workgroup per CU) twice that: the tail balances better with the second
+  // half of the grid scheduled as the first half drains (measured)
+  const uint32_t w = p->fs_wg_per_cu ? p->fs_wg_per_cu : kWide ? 2 : occupancy<kFirst, kR, kWide, kEpi, kRing>();
   const uint32_t g = std::max(16u, (p->num_cus * w) / 16 * 16);
   return std::min(g, (items + 15) / 16 * 16);
+}
+
+// Each of `groups` walkers' number of polynomials; the first `extra` take one more.
+void share_out(FsTable& t, uint32_t groups) {
+  t.share = t.total / groups;
+  t.extra = t.total % groups;
 }
 
 template <bool kFirst, int kR, bool kWide, bool kEpi, int kRing>
@@ -442,6 +404,7 @@ void launch_ring(const tfhe_ntt_plan_s* p, FsTable t, hipStream_t s) {
   using G = Geo<kFirst, kR, kWide>;
   t.ipp_log = t.log_n - (kWide ? 13 : 12);  // items per polynomial: N / item words
   const uint32_t grid = grid_size<kFirst, kR, kWide, kEpi, kRing>(p, t.total << t.ipp_log);
+  share_out(t, grid / 16);
   TFHE_TIMED(kFirst ? K_FS_PASS1 : K_FS_PASS2, s,
              hipLaunchKernelGGL((fs_pass<kFirst, kR, kWide, kEpi, kRing>), dim3(grid), dim3(G::threads), 0, s, t));
 }
@@ -580,9 +543,8 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
   const FourStepLimb* cur = nullptr;
   v4i opA[4], opB[4];
   uint2 tw[4];
-  uint32_t q = 0, qneg = 0, nq = 0;
-  uint64_t cq = 0;
-  ModConst m{};
+  Red R{};
+  uint32_t m_r = 0, m_rp = 0;  // 2^32 mod q and its companion
   uint64_t s0[4][4], s1[4][4];  // sums of products, kept below q 2^32
   issue_source(p, 0, 0);
   bool stored_after = false;  // the previous task ended its item (8 stores after this source)
@@ -604,17 +566,17 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
     if (jd == 0 && limbs + p.pl != cur) {
       // rare: completed here, so that the pipeline carries no wait on these
       cur = limbs + p.pl;
-      const FourStepLimb L = *cur;
-      q = L.q;
-      qneg = L.qneg;
-      nq = 0u - q;
-      cq = (uint32_t)(0x80808080u - q);
-      m = mods[p.pl];
+      const auto* L = (const_as FourStepLimb*)cur;
+      R = make_red(L->q, L->qneg);
+      const auto* m = (const_as ModConst*)mods + p.pl;
+      m_r = m->r;
+      m_rp = m->rp;
+      const PassTables* P = L->pass2;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        opA[j] = *(const v4i*)&L.pass2->opA[j][lane][0];
-        opB[j] = *(const v4i*)&L.pass2->opB[j][lane][0];
-        tw[j] = L.pass2->twist[lane][j];
+        opA[j] = *(const v4i*)&P->opA[j][lane][0];
+        opB[j] = *(const v4i*)&P->opB[j][lane][0];
+        tw[j] = P->twist[lane][j];
       }
       // the builtin (unlike an asm wait) tells the compiler these registers
       // are ready, so it adds no vmcnt(0) at their first use downstream
@@ -637,6 +599,7 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
 #pragma unroll
         for (int e = 0; e < 4; ++e) s0[j][e] = s1[j][e] = 0;
     }
+    const uint32_t q = R.q;
     if (jd != p.own) {
       uint4 rows[4];
 #pragma unroll
@@ -645,8 +608,7 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
         rows[c] = *(const uint4*)(src + (row / G::Rs) * G::pitch + (wave * G::Rs + row % G::Rs) * 4);
       }
       uint4 res[4];
-      auto body = [&](auto big_q) {
-        constexpr bool kBigQ = decltype(big_q)::value;
+      {
         const v4i bias = {(int)q, (int)q, (int)q, (int)q};
         const v4i zero = {0, 0, 0, 0};
 #pragma unroll
@@ -662,23 +624,21 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
           v4i z;
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            z[j] = (int)twist_digits<kBigQ>(fuse_redc(a0[j], a1[j], a2[j], a3[j], q, qneg), tw[j], q, nq, cq);
+            z[j] = (int)twist_digits(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw[j], R);
           const v4i b0 = mfma(opB[0], z, bias);
           const v4i b1 = mfma(opB[1], z, zero);
           const v4i b2 = mfma(opB[2], z, bias);
           const v4i b3 = mfma(opB[3], z, zero);
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            const uint32_t r = reduce_once(fuse_redc(b0[j], b1[j], b2[j], b3[j], q, qneg), q);
+            const uint32_t r = reduce_once(fuse_redc(b0[j], b1[j], b2[j], b3[j], R), q);
             if (sg == 0) res[j].x = r;
             else if (sg == 1) res[j].y = r;
             else if (sg == 2) res[j].z = r;
             else res[j].w = r;
           }
         }
-      };
-      if (q > 0x7F7F7F7Fu) body(std::true_type{});
-      else body(std::false_type{});
+      }
       lds_barrier();  // every wave has read the source
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -699,7 +659,7 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
     auto mac = [&](uint64_t* acc, const v4u& y, const v4u& kk) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const uint64_t v = mad_u64(y[e], kk[e], acc[e]);
+        const uint64_t v = (uint64_t)y[e] * kk[e] + acc[e];
         const uint32_t hi = (uint32_t)(v >> 32);
         acc[e] = ((uint64_t)min(hi, hi - q) << 32) | (uint32_t)v;
       }
@@ -715,8 +675,8 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
     if (stored_after) {
       // s mod q: one Montgomery step (s + m q < 2q 2^32), then times 2^32
       auto fin = [&](uint64_t v) {
-        const uint32_t mm = (uint32_t)v * qneg;
-        return mul_shoup(reduce_once((uint32_t)(mad_u64(mm, q, v) >> 32), q), m.r, m.rp, q);
+        const uint32_t mm = (uint32_t)v * R.qneg;
+        return mul_shoup(reduce_once((uint32_t)(((uint64_t)mm * q + v) >> 32), q), m_r, m_rp, q);
       };
       const uint32_t ext = Gr.level + set.K;
       uint32_t* o0 = Gr.acc + ((uint64_t)p.t * Gr.batch + p.b) * N;
@@ -767,7 +727,7 @@ __device__ __forceinline__ uint32_t redc96(uint64_t acc, uint32_t k, uint32_t q,
   const uint64_t t = mac96(m1, q, acc, k);  // low word 0
   const uint32_t th = (uint32_t)(t >> 32);
   const uint32_t m2 = th * qneg;
-  const uint32_t u = (uint32_t)(mad_u64(m2, q, ((uint64_t)k << 32) | th) >> 32);
+  const uint32_t u = (uint32_t)(((uint64_t)m2 * q + (((uint64_t)k << 32) | th)) >> 32);
   return reduce_once(u, q);
 }
 
@@ -781,7 +741,7 @@ co_pass(const FsTable tab) {
   __shared__ __attribute__((aligned(16))) uint32_t mats[512];  // WA[s][u] then WB[t][v] (broadcast reads)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lo16 = tid & 15, col = tid >> 4;  // level A: v = lo16; level B: s = lo16
-  const Walk walk = make_walk(tab.total, tab.ipp_log);
+  const Walk walk = make_walk(tab);
   if (walk.p >= walk.p_end) return;
   const uint32_t S = tab.cols, c0 = walk.blk * G::W;
 
@@ -794,7 +754,7 @@ co_pass(const FsTable tab) {
     ld_off[j] = kFirst ? natural : tiled;
     st_off[j] = natural;
   }
-  uint32_t kf = 0, kc = 0;
+  uint32_t kf = find_unit(tab.begin, tab.count, walk.p), kc = kf;
   auto issue = [&](uint32_t p, int stage) {
     const Item it = locate(tab, p, kf);
     issue_tile<G::pitch>(tab.u[it.unit].in + it.poly_base, ld_off, ring + stage * G::tile, wave);
@@ -895,6 +855,7 @@ void co_launch(const tfhe_ntt_plan_s* p, FsTable t, hipStream_t s) {
   const uint32_t w = p->fs_wg_per_cu ? p->fs_wg_per_cu : (uint32_t)occupancy_cached(occ, co_pass<kFirst>, 256);
   const uint32_t items = t.total << t.ipp_log;
   const uint32_t grid = std::min(std::max(16u, (p->num_cus * w) / 16 * 16), (items + 15) / 16 * 16);
+  share_out(t, grid / 16);
   TFHE_TIMED(kFirst ? K_CO_PASS1 : K_CO_PASS2, s,
              hipLaunchKernelGGL((co_pass<kFirst>), dim3(grid), dim3(256), 0, s, t));
 }
@@ -950,8 +911,8 @@ hipError_t fs_run_units(const NttUnit* units, uint32_t count, void* ws, hipStrea
     const bool inverse = units[lead].inverse;
     const bool epi = units[lead].acc != nullptr;
     const bool p1only = units[lead].pass1_only;
-    const bool bcast = units[lead].in_bcast;
-    if ((epi || p1only || bcast) && inverse) return hipErrorInvalidValue;
+    const bool bcast = units[lead].in_bcast, out_tiled = units[lead].out_tiled;
+    if (((epi || p1only || bcast) && inverse) || (out_tiled && (!inverse || log_n < 15))) return hipErrorInvalidValue;
     const tfhe_ntt_plan_s* p0 = units[lead].plan;
     const uint32_t N = 1u << log_n, N1 = N >> 8, r = N1 / 16;
     FsTable t1, t2;
@@ -965,17 +926,26 @@ hipError_t fs_run_units(const NttUnit* units, uint32_t count, void* ws, hipStrea
     for (uint32_t k = lead; k < count; ++k) {
       const NttUnit& u = units[k];
       if (!done[k] && u.plan->log_n == log_n && u.inverse == inverse && (u.acc != nullptr) == epi &&
-          u.pass1_only == p1only && u.in_bcast == bcast)
+          u.pass1_only == p1only && u.in_bcast == bcast && u.out_tiled == out_tiled)
         group_polys += (uint64_t)u.limb_count * u.batch;
     }
-    const bool one = !epi && !p1only && !bcast && use_onepass(p0, group_polys);
+    const bool one = !epi && !p1only && !bcast && !out_tiled && use_onepass(p0, group_polys);
+    std::vector<const NttUnit*> cv_units;
+    std::vector<uint32_t*> cv_mids;
+    hipError_t err = hipSuccess;
     auto flush = [&]() {
-      if (t1.total == 0) return;
+      if (bcast) {  // the first pass's input is a broadcast or converted plane
+        const hipError_t e = cv_run(p0, cv_units.data(), cv_mids.data(), (uint32_t)cv_units.size(), s);
+        if (e != hipSuccess) err = e;
+        cv_units.clear();
+        cv_mids.clear();
+      }
+      if (t1.total == 0 || err != hipSuccess) return;
       if (one) {
         (void)op_run(p0, inverse, t1, s);
         return;
       }
-      launch_pass_r<true>(p0, r1, t1, s);
+      if (!bcast) launch_pass_r<true>(p0, r1, t1, s);
       if (p1only) return;
       if (!epi) launch_pass_r<false>(p0, r2, t2, s);
       else if (use_wide(p0, t2.cols)) launch_pass<false, 16, true, true>(p0, t2, s);
@@ -986,7 +956,7 @@ hipError_t fs_run_units(const NttUnit* units, uint32_t count, void* ws, hipStrea
     for (uint32_t k = lead; k < count; ++k) {
       const NttUnit& u = units[k];
       if (done[k] || u.plan->log_n != log_n || u.inverse != inverse || (u.acc != nullptr) != epi ||
-          u.pass1_only != p1only || u.in_bcast != bcast)
+          u.pass1_only != p1only || u.in_bcast != bcast || u.out_tiled != out_tiled || (bcast && u.plan != p0))
         continue;
       done[k] = true;
       const uint32_t polys = u.limb_count * u.batch;
@@ -997,13 +967,20 @@ hipError_t fs_run_units(const NttUnit* units, uint32_t count, void* ws, hipStrea
         t1.total = t2.total = 0;
       }
       const FourStepLimb* tabs = (u.inverse ? u.plan->d_fs_inv : u.plan->d_fs_fwd) + u.limb_begin;
-      t1.u[t1.count++] = FsUnit{u.in, one ? u.out : mids[k], tabs, u.batch, t1.total, nullptr, nullptr, 0,
-                                u.in_bcast ? 1u : 0u};
-      t2.u[t2.count++] = FsUnit{mids[k], u.out, tabs, u.batch, t2.total, u.acc, u.epi_mult, u.epi_add ? 1u : 0u, 0};
+      if (bcast) {
+        if (u.limb_begin != 0) return hipErrorInvalidValue;
+        cv_units.push_back(&u);
+        cv_mids.push_back(mids[k]);
+      }
+      t1.begin[t1.count] = t2.begin[t2.count] = t1.total;
+      t1.u[t1.count++] = FsUnit{u.in, one ? u.out : mids[k], tabs, u.batch, div_inv(u.batch), u.twist, nullptr, nullptr, 0, 0};
+      t2.u[t2.count++] = FsUnit{mids[k], u.out, tabs, u.batch, div_inv(u.batch), u.twist, u.acc, u.epi_mult, u.epi_add ? 1u : 0u,
+                               u.out_tiled ? 1u : 0u};
       t1.total += polys;
       t2.total += polys;
     }
     flush();
+    if (err != hipSuccess) return err;
   }
   return hipGetLastError();
 }
@@ -1047,8 +1024,9 @@ hipError_t co_transform(const tfhe_ntt_plan_s* p, bool inverse, const uint32_t* 
   t1.total = t2.total = limb_count * batch;
   t1.log_n = t2.log_n = p->log_n;
   t1.cols = t2.cols = 256;  // N = 2^16: both passes are 256 x 256
-  t1.u[0] = FsUnit{in, (uint32_t*)ws, tabs, batch, 0, nullptr, nullptr, 0, 0};
-  t2.u[0] = FsUnit{(const uint32_t*)ws, out, tabs, batch, 0, nullptr, nullptr, 0, 0};
+  t1.begin[0] = t2.begin[0] = 0;
+  t1.u[0] = FsUnit{in, (uint32_t*)ws, tabs, batch, div_inv(batch), nullptr, nullptr, nullptr, 0, 0};
+  t2.u[0] = FsUnit{(const uint32_t*)ws, out, tabs, batch, div_inv(batch), nullptr, nullptr, nullptr, 0, 0};
   co_launch<true>(p, t1, s);
   co_launch<false>(p, t2, s);
   return hipGetLastError();

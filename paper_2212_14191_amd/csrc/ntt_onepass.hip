@@ -93,6 +93,9 @@ op_kernel(const FsTable tab) {
   constexpr bool kUA = kInv;       // second-pass level-A index u = g + 4c
   static_assert(St1 >= 1 && St2 >= 1 && CH >= 1, "shape");
   static_assert(3 * CH <= 63, "vmcnt range");
+  // the step factor's lazy products stay below (2 - 2^{1 - St1}) q, so the
+  // post-twist's input stays below 1.94 q (twist_digits)
+  static_assert(St1 <= 4, "post-twist range");
   // polynomial buffers, then the limb's matrix-core operands and twists
   // (both passes) and the per-lane post-twist factors, staged once per limb
   // (the post-twist factors stay in global memory, read per polynomial
@@ -104,11 +107,12 @@ op_kernel(const FsTable tab) {
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int i16 = lane & 15, g = lane >> 4;
-  const uint32_t p_begin = (uint32_t)((uint64_t)blockIdx.x * tab.total / gridDim.x);
-  const uint32_t p_end = (uint32_t)((uint64_t)(blockIdx.x + 1) * tab.total / gridDim.x);
+  const uint32_t p_begin = blockIdx.x * tab.share + min(blockIdx.x, tab.extra);
+  const uint32_t p_end = (blockIdx.x + 1) * tab.share + min(blockIdx.x + 1, tab.extra);
   if (p_begin >= p_end) return;
 
-  uint32_t kf = 0, kc = 0;  // running unit indices of the load and compute walks
+  // running unit indices of the load and compute walks
+  uint32_t kf = find_unit(tab.begin, tab.count, p_begin), kc = kf;
   // direct-to-LDS loads of polynomial p into buffer b: chunk c = wave + k W;
   // LDS slot L of the chunk receives natural quad L ^ X(c, L >> 4)
   auto issue_load = [&](uint32_t p, int b) {
@@ -133,10 +137,9 @@ op_kernel(const FsTable tab) {
   if (NB == 2 && p_begin + 1 < p_end) issue_load(p_begin + 1, 1);
 
   // per-limb values in registers (the rest of the limb's tables is in LDS)
-  const FourStepLimb* cur_limb = nullptr;
+  const void* cur = nullptr;  // whose tables are staged: the limb's, with the unit's twist if it has one
   const uint2* pb_src = nullptr;  // the limb's post-twist factors (global)
-  uint32_t q = 0, qneg = 0, nq = 0;
-  uint64_t cq = 0;
+  Red R{};
   uint2 lb1[4], lb2[16];  // level-B constants (uniform: scalar registers)
   // post-twist step factors: the wave's first step's, and the ratio between
   // consecutive steps of a wave (the factor is geometric in the step index)
@@ -160,23 +163,22 @@ op_kernel(const FsTable tab) {
       wait_vmcnt<0>();  // the loads were issued last
     }
     const FourStepLimb* limb = tab.u[it.unit].limbs + it.limb;
-    if (limb != cur_limb) {
+    const uint2* const twist = kInv ? tab.u[it.unit].twist : nullptr;
+    const void* const key = twist ? (const void*)(twist + it.limb * 256) : limb;
+    if (key != cur) {
       // rare (a few times per workgroup), and every wave is past the
       // previous polynomial's last barrier, so the staged tables are free:
       // copy the new limb's into LDS (waiting here keeps the pipeline free
       // of waits on these loads)
-      const FourStepLimb L = *limb;
-      const PassTables* T1 = L.pass1;
-      const OnePassTables* O = L.op;
-      q = L.q;
-      qneg = L.qneg;
-      nq = 0u - q;
-      cq = (uint32_t)(0x80808080u - q);
+      const auto* L = (const_as FourStepLimb*)limb;
+      const PassTables* T1 = L->pass1;
+      const OnePassTables* O = L->op;
+      R = make_red(L->q, L->qneg);
       const uint32_t* srcs[5] = {&T1->opA[0][0][0], (const uint32_t*)&T1->twist[0][0], &O->p2.opA[0][0][0],
-                                 (const uint32_t*)&O->p2.twist[0][0], (const uint32_t*)&O->post_b[0][0][0]};
+                                 (const uint32_t*)(twist ? twist + it.limb * 256 : &O->p2.twist[0][0]), (const uint32_t*)&O->post_b[0][0][0][0]};
       const int offs[5] = {kTabOpA1, kTabTw1, kTabOpA2, kTabTw2, kTabPb};
       const int lens[5] = {1024, 512, 1024, 512, 2048};
-      pb_src = &O->post_b[0][0][0];
+      pb_src = &O->post_b[0][0][0][0];
 #pragma unroll
       for (int k = 0; k < (kPbLds ? 5 : 4); ++k)
         for (int i = 4 * tid; i < lens[k]; i += 4 * 64 * W)
@@ -193,10 +195,11 @@ op_kernel(const FsTable tab) {
         for (int i = 0; i < 16; ++i) lb2[i] = O->p2.lb[i];
       }
       __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-      cur_limb = limb;
+      cur = key;
     }
     lds_barrier();  // the polynomial is in LDS (every wave's loads landed)
 
+    const uint32_t q = R.q;
     const v4i bias = {(int)q, (int)q, (int)q, (int)q};
     const v4i zero = {0, 0, 0, 0};
 
@@ -213,8 +216,8 @@ op_kernel(const FsTable tab) {
         tw1[j] = *(const uint2*)(lds + kTabTw1 + (lane * 4 + j) * 2);
 #pragma unroll
         for (int sg = 0; sg < 4; ++sg)
-          pb[j][sg] = kPbLds ? *(const uint2*)(lds + kTabPb + ((lane * 4 + j) * 4 + sg) * 2)
-                             : pb_src[(lane * 4 + j) * 4 + sg];
+          pb[j][sg] = kPbLds ? *(const uint2*)(lds + kTabPb + (((sg * 2 + j / 2) * 64 + lane) * 2 + j % 2) * 2)
+                             : pb_src[((sg * 2 + j / 2) * 64 + lane) * 2 + j % 2];
       }
       uint32_t pa[4] = {pa0[0], pa0[1], pa0[2], pa0[3]};
 #pragma unroll
@@ -223,7 +226,7 @@ op_kernel(const FsTable tab) {
         const int ai = opaque(i16), ag = opaque(g);  // for addresses
         if (st > 0) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) pa[j] = mont_mul_lazy(pa[j], pad[j], q, qneg);
+          for (int j = 0; j < 4; ++j) pa[j] = mont_mul_lazy(pa[j], pad[j], R);
         }
         uint4 rows[4];
 #pragma unroll
@@ -243,7 +246,7 @@ op_kernel(const FsTable tab) {
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
             const uint32_t w = sg == 0 ? rows[c].x : sg == 1 ? rows[c].y : sg == 2 ? rows[c].z : rows[c].w;
-            x[c] = (int)balanced_digits(kBigQ ? to_window(w, q) : (int32_t)w);
+            x[c] = (int)(kBigQ ? residue_digits_big(w, q) : residue_digits(w));
           }
           const v4i a0 = mfma(x, opA1[0], bias);
           const v4i a1 = mfma(x, opA1[1], zero);
@@ -254,7 +257,7 @@ op_kernel(const FsTable tab) {
             v4i z;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              z[j] = (int)twist_digits<kBigQ>(fuse_redc(a0[j], a1[j], a2[j], a3[j], q, qneg), tw1[j], q, nq, cq);
+              z[j] = (int)twist_digits(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw1[j], R);
             // level B (only the inverse's 256-point stage here): the same
             // symmetric matrix, unscaled, so opB equals opA
             const v4i b0 = mfma(opA1[0], z, bias);
@@ -262,17 +265,17 @@ op_kernel(const FsTable tab) {
             const v4i b2 = mfma(opA1[2], z, bias);
             const v4i b3 = mfma(opA1[3], z, zero);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) y[j] = fuse_redc(b0[j], b1[j], b2[j], b3[j], q, qneg);
+            for (int j = 0; j < 4; ++j) y[j] = fuse_redc(b0[j], b1[j], b2[j], b3[j], R);
           } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              y[j] = reduce_once(mul_shoup_lazy(fuse_redc(a0[j], a1[j], a2[j], a3[j], q, qneg), tw1[j].x,
+              y[j] = reduce_once(mul_shoup_lazy(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw1[j].x,
                                                 tw1[j].y, q), q);
             level_b<kR1>(y, lb1, rj, g, q);
           }
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            o[j][sg] = twist_digits<kBigQ>(mont_mul_lazy(y[j], pa[j], q, qneg), pb[j][sg], q, nq, cq);
+            o[j][sg] = twist_digits(mont_mul_lazy(y[j], pa[j], R), pb[j][sg], R);
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -292,8 +295,7 @@ op_kernel(const FsTable tab) {
     // vector m take row R0 + 4m + sg; lane (i, g), dword c reads element
     // kR2 u + i % kR2 (u = 4g + c, or g + 4c for the inverse).
     uint4 res[St2][4];
-    auto pass2 = [&](auto big_q) {
-      constexpr bool kBigQ = decltype(big_q)::value;
+    {
       v4i opA2[4];
       uint2 tw2[4];
 #pragma unroll
@@ -333,17 +335,17 @@ op_kernel(const FsTable tab) {
             v4i z;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              z[j] = (int)twist_digits<kBigQ>(fuse_redc(a0[j], a1[j], a2[j], a3[j], q, qneg), tw2[j], q, nq, cq);
+              z[j] = (int)twist_digits(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw2[j], R);
             const v4i b0 = mfma(opA2[0], z, bias);  // level B: the same symmetric matrix
             const v4i b1 = mfma(opA2[1], z, zero);
             const v4i b2 = mfma(opA2[2], z, bias);
             const v4i b3 = mfma(opA2[3], z, zero);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) y[j] = reduce_once(fuse_redc(b0[j], b1[j], b2[j], b3[j], q, qneg), q);
+            for (int j = 0; j < 4; ++j) y[j] = reduce_once(fuse_redc(b0[j], b1[j], b2[j], b3[j], R), q);
           } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              y[j] = reduce_once(mul_shoup_lazy(fuse_redc(a0[j], a1[j], a2[j], a3[j], q, qneg), tw2[j].x,
+              y[j] = reduce_once(mul_shoup_lazy(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw2[j].x,
                                                 tw2[j].y, q), q);
             level_b<kR2>(y, lb2, rj, g, q);
 #pragma unroll
@@ -358,10 +360,7 @@ op_kernel(const FsTable tab) {
           }
         }
       }
-    };
-    // (only the 256-point second stage re-slices with the digit window)
-    if (kR2 == 16 && q > 0x7F7F7F7Fu) pass2(std::true_type{});
-    else pass2(std::false_type{});
+    }
     lds_barrier();  // every wave has read its rows
 #pragma unroll
     for (int st = 0; st < St2; ++st) {
@@ -412,12 +411,14 @@ op_kernel(const FsTable tab) {
 }
 
 template <int kLogN, bool kInv>
-void op_launch(const tfhe_ntt_plan_s* p, const FsTable& t, hipStream_t s) {
+void op_launch(const tfhe_ntt_plan_s* p, FsTable t, hipStream_t s) {
   using C = OpCfg<kLogN, kInv>;
   static std::atomic<int> occ{0};
   const uint32_t w =
       p->fs_wg_per_cu ? p->fs_wg_per_cu : (uint32_t)occupancy_cached(occ, op_kernel<kLogN, kInv>, 64 * C::waves);
   const uint32_t grid = std::min(std::max(1u, p->num_cus * w), t.total);
+  t.share = t.total / grid;
+  t.extra = t.total % grid;
   TFHE_TIMED(K_OP, s, hipLaunchKernelGGL((op_kernel<kLogN, kInv>), dim3(grid), dim3(64 * C::waves), 0, s, t));
 }
 

@@ -175,7 +175,7 @@ static void build_post(uint2* post, int r, int ncols, uint32_t q, uint32_t scale
       }
 }
 
-// One-pass kernel: the first pass's post-twist P(col, out) split into a
+// One-pass and conversion-fused kernels: the first pass's post-twist P(col, out) split into a
 // per-lane factor and a per-step factor (see OnePassTables).
 template <typename F>
 static void build_onepass_post(OnePassTables& op, int r1, int ncols, uint32_t q, uint32_t scale, F P) {
@@ -189,11 +189,12 @@ static void build_onepass_post(OnePassTables& op, int r1, int ncols, uint32_t q,
       const int out = lane % 16 + 16 * t;
       for (int sg = 0; sg < 4; ++sg) {
         const uint32_t w = mulm(P(4 * m + sg, out), scale, q);
-        op.post_b[lane][j][sg] = make_uint2(w, shoup_companion(w, q));
+        op.post_b[sg][j / 2][lane][j % 2] = make_uint2(w, shoup_companion(w, q));
       }
-      const uint32_t base_inv = inv_mod(P(4 * m, out), q);
-      for (int st = 0; st < steps; ++st)
-        op.post_a[st][lane][j] = mulm(mulm(P(4 * st * mt + 4 * m, out), base_inv, q), r32, q);
+      // geometric in the step: P(4 st mt + 4 m, out) / P(4 m, out)
+      const uint32_t ratio = mulm(P(4 * mt % ncols, out), inv_mod(P(0, out), q), q);
+      uint32_t f = r32;
+      for (int st = 0; st < steps; ++st, f = mulm(f, ratio, q)) op.post_a[st][lane][j] = f;
     }
 }
 
@@ -280,8 +281,8 @@ static void build_fourstep_limb(FsHostLimb& L, uint32_t log_n, uint32_t q, uint3
           WB[a][b] = WA[a][b];
         }
       build_pass(L.op.p2, 16, WA, T, WB, q, 1, nullptr);
-      build_onepass_post(L.op, r, 256, q, 1, P);
     }
+    build_onepass_post(L.op, r, 256, q, r == 16 ? r32 : 1, P);
   } else {
     cyc256(L.p1, omi, 1);
     if (r == 16) {
@@ -311,6 +312,23 @@ static void build_fourstep_limb(FsHostLimb& L, uint32_t log_n, uint32_t q, uint3
     if (r == 16) co_post(P);
     if (r < 16) build_onepass_post(L.op, 16, (int)N1, q, r32, P);
   }
+}
+
+// The second inverse pass's twist (PassTables::twist as build_fourstep_limb
+// lays it out) times `scale`: phi^{-(2v+1)s}, with N^{-1} where level B is a
+// butterfly (r < 16).
+void scaled_twist(const tfhe_ntt_plan_s* p, uint32_t limb, uint32_t scale, std::vector<uint2>& out) {
+  const uint32_t q = p->q[limb], N1 = p->n / 256, r = N1 / 16;
+  const uint32_t phii = inv_mod(pow_mod(p->psi[limb], 256, q), q);
+  uint32_t f = mulm(scale % q, (uint32_t)((1ull << 32) % q), q);
+  if (r < 16) f = mulm(f, inv_mod(p->n % q, q), q);
+  for (uint32_t lane = 0; lane < 64; ++lane)
+    for (uint32_t j = 0; j < 4; ++j) {
+      const uint32_t s = lane % 16, v = (4 * (lane / 16) + j) % r;
+      // r = 16: T[s][v] = phi^{-(2v+1)s}; r < 16: phi^{-(2v+1)s} as well, [s][v]
+      const uint32_t w = mulm(pow_mod(phii, (uint64_t)(2 * v + 1) * s, q), f, q);
+      out.push_back(make_uint2(w, shoup_companion(w, q)));
+    }
 }
 
 template <typename T>
@@ -355,13 +373,14 @@ tfhe_status plan_build(tfhe_ntt_plan_s* p) {
   p->has_co = p->has_mfma && p->log_n == 16;
   if (p->has_mfma) {
     // blob: per limb and direction {PassTables p1, p2, post[256*64*4]} and,
-    // for N = 2^16, {CoPass c1, c2, co_post[256*256]}
+    // for N = 2^16, {CoPass c1, c2, co_post[256*256]}; then OnePassTables
     const size_t post_elems = 256 * 64 * 4;
     const bool co = p->log_n == 16;
     const size_t co_bytes = co ? 2 * sizeof(CoPass) + 256 * 256 * sizeof(uint2) : 0;
-    const bool one = p->log_n <= 15;  // one-pass kernel tables
-    const size_t op_bytes = one ? sizeof(OnePassTables) : 0;
-    const size_t per = 2 * sizeof(PassTables) + post_elems * sizeof(uint2) + co_bytes + op_bytes;
+    const size_t op_off = 2 * sizeof(PassTables) + post_elems * sizeof(uint2) + co_bytes;
+    const size_t per = op_off + sizeof(OnePassTables);
+    p->fs_limb_bytes = per;
+    p->fs_op_off = op_off;
     const size_t total = per * 2 * L;
     std::vector<unsigned char> blob(total);
     std::vector<FourStepLimb> hf(L), hi(L);
@@ -371,7 +390,7 @@ tfhe_status plan_build(tfhe_ntt_plan_s* p) {
     unsigned char* dbase = (unsigned char*)p->d_fs_blob;
     for (uint32_t l = 0; l < L; ++l)
       for (int dir = 0; dir < 2; ++dir) {
-        FsHostLimb H;
+        FsHostLimb H{};
         build_fourstep_limb(H, p->log_n, p->q[l], p->psi[l], dir);
         size_t off = per * (2 * l + dir);
         memcpy(&blob[off], &H.p1, sizeof(PassTables));
@@ -383,12 +402,8 @@ tfhe_status plan_build(tfhe_ntt_plan_s* p) {
         f.post1 = (const uint2*)(dbase + off + 2 * sizeof(PassTables));
         f.co1 = f.co2 = nullptr;
         f.co_post = nullptr;
-        f.op = nullptr;
-        if (one) {
-          const size_t o3 = off + 2 * sizeof(PassTables) + post_elems * sizeof(uint2) + co_bytes;
-          memcpy(&blob[o3], &H.op, sizeof(OnePassTables));
-          f.op = (const OnePassTables*)(dbase + o3);
-        }
+        memcpy(&blob[off + op_off], &H.op, sizeof(OnePassTables));
+        f.op = (const OnePassTables*)(dbase + off + op_off);
         if (co) {
           const size_t o2 = off + 2 * sizeof(PassTables) + post_elems * sizeof(uint2);
           memcpy(&blob[o2], &H.c1, sizeof(CoPass));

@@ -36,7 +36,7 @@ const char* kNames[] = {"ntt_mfma_pass1", "ntt_mfma_pass2", "ntt_bf_single", "nt
                         "ckks_inner",     "ckks_moddown_conv", "ckks_moddown_final", "frobenius",
                         "ckks_rescale_bcast", "ckks_rescale_final",
                         "ntt_co_pass1",       "ntt_co_pass2",       "ntt_mfma_onepass",
-                        "ntt_mfma_pass2_inner"};
+                        "ntt_mfma_pass2_inner",  "ntt_mfma_conv_pass1"};
 constexpr int kNumNames = sizeof(kNames) / sizeof(kNames[0]);
 }  // namespace
 
