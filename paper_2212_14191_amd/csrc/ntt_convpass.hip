@@ -185,16 +185,14 @@ cv_pass(const CvTable tab) {
     const uint32_t* src = U.in + ((uint64_t)b << log_n) + row * rs + quad * qs;
 #pragma unroll
     for (int r = 0; r < kPlanes; ++r) {
-      if (kIn == 0 || r < (int)U.nin) {
+      // (an input that is not there has zero constants: the last one again,
+      // since a branch around its loads would wait for them before the next)
+      const uint64_t at = min((uint32_t)r, U.nin - 1) * plane;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const v4u w = *(const v4u*)(src + r * plane + c * kR * rs);
+      for (int c = 0; c < 4; ++c) {
+        const v4u w = *(const v4u*)(src + at + c * kR * rs);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) y[r][4 * c + i] = w[i];
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) y[r][e] = 1u << 30;
+        for (int i = 0; i < 4; ++i) y[r][4 * c + i] = w[i];
       }
     }
     if (kIn) {
