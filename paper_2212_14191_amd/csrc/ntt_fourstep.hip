@@ -874,16 +874,28 @@ size_t fs_workspace_bytes(const tfhe_ntt_plan_s* p, uint32_t limb_count, uint32_
 }
 
 // Whether a launch of `polys` four-step transforms of this plan takes the
-// one-pass kernel: always with fs_passes 1, never with 2; by default at
-// N = 2^12..2^14 when the launch gives every CU at least two polynomials
-// (one workgroup holds one whole polynomial, so a smaller launch leaves CUs
-// idle: HMULT at N = 2^14, batch 1-4, ran 10-20 % slower with every
-// transform on it; with the rule HMULT at batch 8-64 is 2-8 % faster at
-// 2^12..2^14 and unchanged below; at 2^15 the kernel is slower).
-static bool use_onepass(const tfhe_ntt_plan_s* p, uint64_t polys) {
+// one-pass kernel: always with fs_passes 1, never with 2.  By default where it
+// measured faster than two passes (us, one pass : two passes, forward, C = 256
+// CUs; the inverse lies within 5 % of it):
+//   2^12  always: 5.6 : 6.9 (8 polynomials), 8.5 : 10.3 (512);
+//   2^13  7.7 : 7.7 (64), 8.0 : 8.4 (128), 8.7 : 10.9 (256), 13.4 : 12.8 (320),
+//         13.5 : 13.7 (384), 14.5 : 23.5 (508);
+//   2^14  13.9 : 12.9 (128), 13.8 : 14.8 (144), 15.9 : 25.1 (256), 24.1 : 24.9
+//         (264), 25.8 : 37.6 (508);
+//   2^15  forward 29.2 : 26.7 (128), 28.7 : 31.5 (144), 31.9 : 40.8 (256), 55.8 :
+//         42.2 (264), 62.8 : 66.2 (508); inverse 36.4 : 36.2 (256), else slower.
+// A workgroup holds one whole polynomial, so few polynomials leave CUs idle,
+// and a little more than one (2^15: any more) per CU means a second round.
+static bool use_onepass(const tfhe_ntt_plan_s* p, bool inverse, uint64_t polys) {
   if (!op_supported(p->log_n) || p->fs_passes == 2) return false;
   if (p->fs_passes == 1) return true;
-  return p->log_n <= 14 && polys >= 2ull * p->num_cus;
+  const uint64_t C = p->num_cus;
+  switch (p->log_n) {
+    case 12: return true;
+    case 13: return 2 * polys >= C && (polys <= C || 2 * polys >= 3 * C);
+    case 14: return 2 * polys > C;
+    default: return !inverse && 2 * polys > C && polys <= C;
+  }
 }
 
 // Fused launches: units are grouped by (N, direction), in order of first
@@ -929,7 +941,7 @@ hipError_t fs_run_units(const NttUnit* units, uint32_t count, void* ws, hipStrea
           u.pass1_only == p1only && u.in_bcast == bcast && u.out_tiled == out_tiled)
         group_polys += (uint64_t)u.limb_count * u.batch;
     }
-    const bool one = !epi && !p1only && !bcast && !out_tiled && use_onepass(p0, group_polys);
+    const bool one = !epi && !p1only && !bcast && !out_tiled && use_onepass(p0, inverse, group_polys);
     std::vector<const NttUnit*> cv_units;
     std::vector<uint32_t*> cv_mids;
     hipError_t err = hipSuccess;

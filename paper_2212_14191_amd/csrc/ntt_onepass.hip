@@ -13,8 +13,11 @@
 // stores.  For N <= 2^14 a workgroup has 4 waves and one polynomial buffer,
 // so that two or three workgroups share a CU: one's loads and stores overlap
 // the others' arithmetic (measured faster than one 8-wave workgroup that
-// double-buffers: 1.2-1.25 x at 2^13 and 2^14).  At 2^15 the polynomial
-// takes 128 KiB and one workgroup of 8 waves owns the CU.
+// double-buffers: 1.2-1.25 x at 2^13 and 2^14).  A launch of no more
+// polynomials than CUs has nothing to overlap and takes 8 waves at 2^13 and
+// 2^14 (256 polynomials: 9.7 -> 8.7 and 17.4 -> 15.8 us; 16 waves at 2^14
+// have too few registers: 24.8).  At 2^15 the polynomial takes 128 KiB and one
+// workgroup of 8 waves owns the CU.
 //
 // LDS layout: 1 KiB chunks of the polynomial in order; inside a chunk the
 // 16-byte quads are XOR-swizzled (quad Q at Q ^ X, X a function of the chunk
@@ -33,7 +36,7 @@
 namespace tfhe {
 namespace {
 
-// Per (log N, direction): waves per workgroup, polynomial buffers, and the
+// Per (log N, direction): waves per workgroup of a large launch, polynomial buffers, and the
 // swizzle constants: input X = (a c + b (Q >> 4)) & 15; output
 // X = (a c + b (Q >> sh)) & (2^sh - 1), with c the chunk and Q the quad.
 template <int kLogN, bool kInv>
@@ -79,15 +82,15 @@ __device__ __forceinline__ int opaque(int x) {
   return x;
 }
 
-template <int kLogN, bool kInv>
-__global__ void __launch_bounds__((64 * OpCfg<kLogN, kInv>::waves), (OpCfg<kLogN, kInv>::waves <= 4 ? 2 : 1))
+template <int kLogN, bool kInv, int W>
+__global__ void __launch_bounds__((64 * W), (W <= 4 ? 2 : W / 4))
 op_kernel(const FsTable tab) {
   using C = OpCfg<kLogN, kInv>;
   constexpr int N = 1 << kLogN, N1 = N >> 8;
   constexpr int kR1 = kInv ? 16 : N1 / 16, kR2 = kInv ? N1 / 16 : 16;
   constexpr int P1 = 16 * kR1, S = N / P1;   // pass 1: S columns of P1 points
   constexpr int Mt1 = 16 / kR1, Mt2 = 16 / kR2;
-  constexpr int W = C::waves, NB = C::bufs;
+  constexpr int NB = C::bufs;
   constexpr int St1 = S / (4 * Mt1) / W, St2 = P1 / (4 * Mt2) / W;  // steps per wave
   constexpr int CH = N / 256 / W;  // 1 KiB chunks per wave and polynomial
   constexpr bool kUA = kInv;       // second-pass level-A index u = g + 4c
@@ -410,16 +413,24 @@ op_kernel(const FsTable tab) {
   }
 }
 
-template <int kLogN, bool kInv>
-void op_launch(const tfhe_ntt_plan_s* p, FsTable t, hipStream_t s) {
-  using C = OpCfg<kLogN, kInv>;
+template <int kLogN, bool kInv, int W>
+void op_launch_w(const tfhe_ntt_plan_s* p, FsTable t, hipStream_t s) {
   static std::atomic<int> occ{0};
   const uint32_t w =
-      p->fs_wg_per_cu ? p->fs_wg_per_cu : (uint32_t)occupancy_cached(occ, op_kernel<kLogN, kInv>, 64 * C::waves);
+      p->fs_wg_per_cu ? p->fs_wg_per_cu : (uint32_t)occupancy_cached(occ, op_kernel<kLogN, kInv, W>, 64 * W);
   const uint32_t grid = std::min(std::max(1u, p->num_cus * w), t.total);
   t.share = t.total / grid;
   t.extra = t.total % grid;
-  TFHE_TIMED(K_OP, s, hipLaunchKernelGGL((op_kernel<kLogN, kInv>), dim3(grid), dim3(64 * C::waves), 0, s, t));
+  TFHE_TIMED(K_OP, s, hipLaunchKernelGGL((op_kernel<kLogN, kInv, W>), dim3(grid), dim3(64 * W), 0, s, t));
+}
+
+template <int kLogN, bool kInv>
+void op_launch(const tfhe_ntt_plan_s* p, const FsTable& t, hipStream_t s) {
+  // no more polynomials than CUs: nothing else runs beside a workgroup
+  if constexpr (kLogN == 13 || kLogN == 14) {
+    if (t.total <= p->num_cus) return op_launch_w<kLogN, kInv, 8>(p, t, s);
+  }
+  op_launch_w<kLogN, kInv, OpCfg<kLogN, kInv>::waves>(p, t, s);
 }
 
 }  // namespace
