@@ -85,7 +85,7 @@ struct IpGroup {
   uint32_t* acc;
   uint32_t level, batch, digits;
   uint32_t key0;   // keys.k index of the group's element 0 (keys.count > 1)
-  uint32_t item0;  // ip_run: the group's first work item (filled in by ip_run)
+  uint32_t item0, batch_inv;  // ip_run: the group's first work item and div_inv(batch) (filled in by ip_run)
 };
 constexpr int kMaxIpGroups = kMaxRotBatch;
 // The inner products of several level groups in one launch.

@@ -18,7 +18,8 @@ constexpr int kMaxUnits = 40;
 struct FsUnit {
   const uint32_t* in;
   uint32_t* out;
-  const FourStepLimb* limbs;  // tables of the unit's first limb
+  const FourStepLimb* limbs;  // the unit's first limb, and its tables (limb l's at
+  const unsigned char* tables;  // tables + l * tab_stride: an address, not a load)
   uint32_t batch, batch_inv;
   // inverse second pass: its twist per limb ([limb][64][4]), null for the plan's
   const uint2* twist;
@@ -35,6 +36,8 @@ struct FsTable {
   uint32_t cols;          // S = N / P: columns of this pass (row stride in natural order)
   uint32_t ipp_log;       // log2 of the items per polynomial (N / item words)
   uint32_t share, extra;  // polynomials of walker a: share, one more for a < extra
+  uint64_t tab_stride;    // of the limbs' tables, in bytes: pass 1's PassTables,
+  uint64_t tab_op;        // pass 2's, pass 1's post-twist; OnePassTables at tab_op
   uint32_t begin[kMaxUnits];  // a unit's first polynomial
   FsUnit u[kMaxUnits];
 };
@@ -214,6 +217,14 @@ __device__ __forceinline__ void issue_tile(const uint32_t* src, const uint32_t* 
   }
 }
 
+// Loads the values (a kernel's arguments) here, together: each line of the
+// arguments is a miss of some 200 ns in the scalar cache, one after the other
+// where the code happens to use them.
+template <typename A, typename B, typename C, typename D, typename E, typename F>
+__device__ __forceinline__ void touch(A a, B b, C c, D d, E e, F f) {
+  asm volatile("" ::"s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f));
+}
+
 struct Item {
   uint32_t unit, limb;
   size_t poly_base;  // word offset of the polynomial within the unit's arrays
@@ -226,10 +237,17 @@ __device__ __forceinline__ uint32_t div_by(uint32_t n, uint32_t d, uint32_t inv)
   const uint32_t k = __umulhi(n, inv);  // the quotient or one more
   return k * d > n ? k - 1 : k;
 }
-// The unit of global polynomial p: the lanes compare one entry each (a walk's
-// start; later polynomials advance the running index in locate).
+// The unit of global polynomial p (a walk's start; later polynomials advance
+// the running index in locate): one scalar load for a few units, else the lanes
+// compare one entry each.
 __device__ __forceinline__ uint32_t find_unit(const uint32_t* begin, uint32_t count, uint32_t p) {
   if (count == 1) return 0;
+  if (count <= 8) {
+    uint32_t k = 0;
+#pragma unroll
+    for (uint32_t i = 1; i < 8; ++i) k += (uint32_t)(i < count) & (uint32_t)(begin[i] <= p);
+    return k;
+  }
   const uint32_t lane = threadIdx.x & 63;
   const bool past = lane < count && begin[lane < count ? lane : 0] <= p;
   return (uint32_t)__popcll(__ballot(past)) - 1;

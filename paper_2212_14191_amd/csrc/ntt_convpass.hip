@@ -93,6 +93,7 @@ cv_pass(const CvTable tab) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i16 = lane & 15, g = lane >> 4;
 
+  touch(tab.count, tab.mods, tab.item_begin[7], tab.u[0].in, tab.u[0].batch, tab.u[0].batch_inv);
   // item -> (unit, chunk, column block, element)
   const uint32_t k = find_unit(tab.item_begin, tab.count, blockIdx.x);
   const CvUnit& U = tab.u[k];

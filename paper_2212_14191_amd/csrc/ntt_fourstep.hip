@@ -120,6 +120,7 @@ fs_pass(const FsTable tab) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint32_t* const gather = kGather ? ring + kRing * G::tile + wave * 1024 : ring;
   const int i16 = lane & 15, g = lane >> 4;
+  touch(tab.count, tab.tab_op, tab.begin[7], tab.u[0].in, tab.u[0].batch_inv, tab.u[0].out_tiled);
   const Walk walk = make_walk(tab);
   if (walk.p >= walk.p_end) return;
   const uint32_t S = tab.cols, c0 = walk.blk * G::W;
@@ -180,7 +181,8 @@ fs_pass(const FsTable tab) {
       // rare (a few times per workgroup): completed here, so that the
       // steady-state path carries no wait on these loads
       const auto* L = (const_as FourStepLimb*)limb;
-      const PassTables* P = kFirst ? L->pass1 : L->pass2;
+      const unsigned char* const base = tab.u[it.unit].tables + it.limb * tab.tab_stride;
+      const PassTables* P = (const PassTables*)base + (kFirst ? 0 : 1);
       R = make_red(L->q, L->qneg);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -201,7 +203,7 @@ fs_pass(const FsTable tab) {
       if (kFirst) {
 #pragma unroll
         for (int sg = 0; sg < 4; ++sg) {
-          const uint2* pp = L->post1 + ((size_t)(c0 + 4 * wave * G::Mt + sg) * 64 + lane) * 4;
+          const uint2* pp = (const uint2*)(P + 2) + ((size_t)(c0 + 4 * wave * G::Mt + sg) * 64 + lane) * 4;
 #pragma unroll
           for (int j = 0; j < 4; ++j) pt[sg][j] = pp[j];
         }
@@ -473,7 +475,7 @@ void launch_pass_r(const tfhe_ntt_plan_s* p, uint32_t r, const FsTable& t, hipSt
 template <bool kWide>
 __global__ void __launch_bounds__(kWide ? 512 : 256, kWide ? 1 : 2)
 ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst* __restrict__ mods,
-        uint32_t log_n, uint32_t ipp, uint32_t items) {
+        uint32_t log_n, uint32_t ipp_log, uint32_t alpha_inv, uint32_t items) {
   using G = Geo<false, 16, kWide>;
   // two source buffers, then the key blocks of components 0 and 1
   __shared__ __attribute__((aligned(16))) uint32_t lds[4 * G::tile];
@@ -502,12 +504,12 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
     while (p.grp + 1 < set.count && set.g[p.grp + 1].item0 <= w) ++p.grp;
     const IpGroup& Gr = set.g[p.grp];
     const uint32_t l = w - Gr.item0;
-    p.b = l % Gr.batch;
-    const uint32_t tb = l / Gr.batch;
-    p.blk = tb % ipp;
-    p.t = tb / ipp;
+    const uint32_t tb = div_by(l, Gr.batch, Gr.batch_inv);
+    p.b = l - tb * Gr.batch;
+    p.blk = tb & ((1u << ipp_log) - 1);
+    p.t = tb >> ipp_log;
     p.pl = p.t < Gr.level ? p.t : set.L + (p.t - Gr.level);  // plan limb
-    p.own = p.t < Gr.level ? p.t / set.alpha : 0xFFFFFFFFu;
+    p.own = p.t < Gr.level ? div_by(p.t, set.alpha, alpha_inv) : 0xFFFFFFFFu;
     return p;
   };
   // 16 bytes per lane into this wave's slot (4 wave + j) of `dst` (output layout)
@@ -536,6 +538,7 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
                            wave);
   };
 
+  touch(set.count, set.g[0].src, set.g[0].batch_inv, set.keys.k[0], limbs, items);
   uint32_t w = blockIdx.x, jd = 0;
   if (w >= items) return;
   Pos p = pos_of(w);
@@ -560,9 +563,6 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
     const bool next = nw < items;
     uint32_t ld[4], st[4];
     offsets(p.blk, ld, st);
-    // this task's source: issued before the previous task's stores (if any)
-    if (stored_after) wait_vmcnt<8>();
-    else wait_vmcnt<0>();
     if (jd == 0 && limbs + p.pl != cur) {
       // rare: completed here, so that the pipeline carries no wait on these
       cur = limbs + p.pl;
@@ -582,6 +582,9 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
       // are ready, so it adds no vmcnt(0) at their first use downstream
       __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     }
+    // this task's source: issued before the previous task's stores (if any)
+    if (stored_after) wait_vmcnt<8>();
+    else wait_vmcnt<0>();
     lds_barrier();  // the source is in LDS; every wave is done with the other buffer and the keys
     // this task's keys, then the next task's source
     const uint32_t* key = set.keys.k[set.keys.count == 1 ? 0 : Gr.key0 + p.b];
@@ -929,6 +932,8 @@ hipError_t fs_run_units(const NttUnit* units, uint32_t count, void* ws, hipStrea
     const uint32_t N = 1u << log_n, N1 = N >> 8, r = N1 / 16;
     FsTable t1, t2;
     t1.log_n = t2.log_n = log_n;
+    t1.tab_stride = t2.tab_stride = 2 * p0->fs_limb_bytes;  // (the same for every plan of this N)
+    t1.tab_op = t2.tab_op = p0->fs_op_off;
     t1.cols = inverse ? N1 : 256;  // N / P of pass 1
     t2.cols = inverse ? 256 : N1;
     const uint32_t r1 = inverse ? 16 : r, r2 = inverse ? r : 16;
@@ -979,15 +984,17 @@ hipError_t fs_run_units(const NttUnit* units, uint32_t count, void* ws, hipStrea
         t1.total = t2.total = 0;
       }
       const FourStepLimb* tabs = (u.inverse ? u.plan->d_fs_inv : u.plan->d_fs_fwd) + u.limb_begin;
+      const unsigned char* blob = (const unsigned char*)u.plan->d_fs_blob +
+                                  (2 * u.limb_begin + (u.inverse ? 1 : 0)) * u.plan->fs_limb_bytes;
       if (bcast) {
         if (u.limb_begin != 0) return hipErrorInvalidValue;
         cv_units.push_back(&u);
         cv_mids.push_back(mids[k]);
       }
       t1.begin[t1.count] = t2.begin[t2.count] = t1.total;
-      t1.u[t1.count++] = FsUnit{u.in, one ? u.out : mids[k], tabs, u.batch, div_inv(u.batch), u.twist, nullptr, nullptr, 0, 0};
-      t2.u[t2.count++] = FsUnit{mids[k], u.out, tabs, u.batch, div_inv(u.batch), u.twist, u.acc, u.epi_mult, u.epi_add ? 1u : 0u,
-                               u.out_tiled ? 1u : 0u};
+      t1.u[t1.count++] = FsUnit{u.in, one ? u.out : mids[k], tabs, blob, u.batch, div_inv(u.batch), u.twist, nullptr, nullptr, 0, 0};
+      t2.u[t2.count++] = FsUnit{mids[k], u.out, tabs, blob, u.batch, div_inv(u.batch), u.twist, u.acc, u.epi_mult,
+                               u.epi_add ? 1u : 0u, u.out_tiled ? 1u : 0u};
       t1.total += polys;
       t2.total += polys;
     }
@@ -1000,20 +1007,21 @@ hipError_t fs_run_units(const NttUnit* units, uint32_t count, void* ws, hipStrea
 template <bool kWide>
 static hipError_t ip_launch(const tfhe_ntt_plan_s* p, IpSet& set, hipStream_t s) {
   using G = Geo<false, 16, kWide>;
-  const uint32_t ipp = p->n / G::item;  // second-pass items per polynomial (>= 1)
+  const uint32_t ipp = p->n / G::item;  // second-pass items per polynomial (a power of two)
   static std::atomic<int> occ{0};
   const int resident = occupancy_cached(occ, ip_pass<kWide>, G::threads);
   uint64_t items = 0;
   for (uint32_t g = 0; g < set.count; ++g) {
     set.g[g].item0 = (uint32_t)items;
+    set.g[g].batch_inv = div_inv(set.g[g].batch);
     items += (uint64_t)(set.g[g].level + set.K) * ipp * set.g[g].batch;
   }
   if (items == 0) return hipSuccess;
-  if (items >= (1ull << 32)) return hipErrorInvalidValue;
+  if (items >= (1ull << 31)) return hipErrorInvalidValue;  // (more than any memory holds)
   const uint32_t grid = (uint32_t)std::min<uint64_t>(items, (uint64_t)p->num_cus * resident);
   TFHE_TIMED(K_IP, s,
              hipLaunchKernelGGL(ip_pass<kWide>, dim3(grid), dim3(G::threads), 0, s, set, p->d_fs_fwd, p->d_mod,
-                                p->log_n, ipp, (uint32_t)items));
+                                p->log_n, (uint32_t)__builtin_ctz(ipp), div_inv(set.alpha), (uint32_t)items));
   return hipGetLastError();
 }
 
@@ -1037,8 +1045,8 @@ hipError_t co_transform(const tfhe_ntt_plan_s* p, bool inverse, const uint32_t* 
   t1.log_n = t2.log_n = p->log_n;
   t1.cols = t2.cols = 256;  // N = 2^16: both passes are 256 x 256
   t1.begin[0] = t2.begin[0] = 0;
-  t1.u[0] = FsUnit{in, (uint32_t*)ws, tabs, batch, div_inv(batch), nullptr, nullptr, nullptr, 0, 0};
-  t2.u[0] = FsUnit{(const uint32_t*)ws, out, tabs, batch, div_inv(batch), nullptr, nullptr, nullptr, 0, 0};
+  t1.u[0] = FsUnit{in, (uint32_t*)ws, tabs, nullptr, batch, div_inv(batch), nullptr, nullptr, nullptr, 0, 0};
+  t2.u[0] = FsUnit{(const uint32_t*)ws, out, tabs, nullptr, batch, div_inv(batch), nullptr, nullptr, nullptr, 0, 0};
   co_launch<true>(p, t1, s);
   co_launch<false>(p, t2, s);
   return hipGetLastError();

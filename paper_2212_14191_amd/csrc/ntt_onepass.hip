@@ -36,27 +36,27 @@
 namespace tfhe {
 namespace {
 
-// Per (log N, direction): waves per workgroup of a large launch, polynomial buffers, and the
+// Per (log N, direction): waves per workgroup of a large launch and the
 // swizzle constants: input X = (a c + b (Q >> 4)) & 15; output
 // X = (a c + b (Q >> sh)) & (2^sh - 1), with c the chunk and Q the quad.
 template <int kLogN, bool kInv>
 struct OpCfg;
-#define TFHE_OPCFG(LN, INV, W, B, IA, IB, OA, OB, OS, PB)                   \
+#define TFHE_OPCFG(LN, INV, W, IA, IB, OA, OB, OS, PB)                      \
   template <>                                                              \
   struct OpCfg<LN, INV> {                                                  \
-    static constexpr int waves = W, bufs = B;                              \
+    static constexpr int waves = W;                                        \
     static constexpr uint32_t in_a = IA, in_b = IB, out_a = OA, out_b = OB; \
     static constexpr uint32_t out_sh = OS;                                 \
     static constexpr bool pb_lds = PB;                                     \
   };
-TFHE_OPCFG(12, false, 4, 1, 1, 4, 0, 1, 4, true)
-TFHE_OPCFG(13, false, 4, 1, 9, 4, 1, 1, 3, true)
-TFHE_OPCFG(14, false, 4, 1, 5, 4, 1, 4, 4, false)
-TFHE_OPCFG(15, false, 8, 1, 9, 4, 1, 4, 4, true)
-TFHE_OPCFG(12, true, 4, 1, 4, 1, 1, 0, 4, true)
-TFHE_OPCFG(13, true, 4, 1, 4, 1, 1, 0, 4, true)
-TFHE_OPCFG(14, true, 4, 1, 4, 1, 1, 0, 4, false)
-TFHE_OPCFG(15, true, 8, 1, 5, 4, 1, 0, 4, true)
+TFHE_OPCFG(12, false, 4, 1, 4, 0, 1, 4, true)
+TFHE_OPCFG(13, false, 4, 9, 4, 1, 1, 3, true)
+TFHE_OPCFG(14, false, 4, 5, 4, 1, 4, 4, false)
+TFHE_OPCFG(15, false, 8, 9, 4, 1, 4, 4, true)
+TFHE_OPCFG(12, true, 4, 4, 1, 1, 0, 4, true)
+TFHE_OPCFG(13, true, 4, 4, 1, 1, 0, 4, true)
+TFHE_OPCFG(14, true, 4, 4, 1, 1, 0, 4, false)
+TFHE_OPCFG(15, true, 8, 5, 4, 1, 0, 4, true)
 #undef TFHE_OPCFG
 
 template <uint32_t kA, uint32_t kB>
@@ -90,35 +90,34 @@ op_kernel(const FsTable tab) {
   constexpr int kR1 = kInv ? 16 : N1 / 16, kR2 = kInv ? N1 / 16 : 16;
   constexpr int P1 = 16 * kR1, S = N / P1;   // pass 1: S columns of P1 points
   constexpr int Mt1 = 16 / kR1, Mt2 = 16 / kR2;
-  constexpr int NB = C::bufs;
   constexpr int St1 = S / (4 * Mt1) / W, St2 = P1 / (4 * Mt2) / W;  // steps per wave
   constexpr int CH = N / 256 / W;  // 1 KiB chunks per wave and polynomial
   constexpr bool kUA = kInv;       // second-pass level-A index u = g + 4c
   static_assert(St1 >= 1 && St2 >= 1 && CH >= 1, "shape");
-  static_assert(3 * CH <= 63, "vmcnt range");
   // the step factor's lazy products stay below (2 - 2^{1 - St1}) q, so the
   // post-twist's input stays below 1.94 q (twist_digits)
   static_assert(St1 <= 4, "post-twist range");
-  // polynomial buffers, then the limb's matrix-core operands and twists
+  // the polynomial, then the limb's matrix-core operands and twists
   // (both passes) and the per-lane post-twist factors, staged once per limb
   // (the post-twist factors stay in global memory, read per polynomial
   // through the caches, where LDS must hold two workgroups' polynomials)
   constexpr bool kPbLds = C::pb_lds;
-  constexpr int kTabOpA1 = NB * N, kTabTw1 = kTabOpA1 + 1024, kTabOpA2 = kTabTw1 + 512;
+  constexpr int kTabOpA1 = N, kTabTw1 = kTabOpA1 + 1024, kTabOpA2 = kTabTw1 + 512;
   constexpr int kTabTw2 = kTabOpA2 + 1024, kTabPb = kTabTw2 + 512, kLdsWords = kTabPb + (kPbLds ? 2048 : 0);
-  __shared__ __attribute__((aligned(16))) uint32_t lds[kLdsWords];
+  __shared__ __attribute__((aligned(16))) uint32_t buf[kLdsWords];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i16 = lane & 15, g = lane >> 4;
+  touch(tab.count, tab.tab_op, tab.begin[7], tab.u[0].in, tab.u[0].batch_inv, tab.u[0].twist);
   const uint32_t p_begin = blockIdx.x * tab.share + min(blockIdx.x, tab.extra);
   const uint32_t p_end = (blockIdx.x + 1) * tab.share + min(blockIdx.x + 1, tab.extra);
   if (p_begin >= p_end) return;
 
   // running unit indices of the load and compute walks
   uint32_t kf = find_unit(tab.begin, tab.count, p_begin), kc = kf;
-  // direct-to-LDS loads of polynomial p into buffer b: chunk c = wave + k W;
+  // direct-to-LDS loads of polynomial p: chunk c = wave + k W;
   // LDS slot L of the chunk receives natural quad L ^ X(c, L >> 4)
-  auto issue_load = [&](uint32_t p, int b) {
+  auto issue_load = [&](uint32_t p) {
     const Item it = locate(tab, p, kf);
     const uint32_t* src = tab.u[it.unit].in + it.poly_base;
     const uint32_t al = (uint32_t)opaque(lane);
@@ -127,7 +126,7 @@ op_kernel(const FsTable tab) {
       const uint32_t c = wave + k * W;
       const uint32_t X = (C::in_a * c + C::in_b * (al >> 4)) & 15u;
       const uint32_t* gp = src + c * 256 + 4 * (al ^ X);
-      const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_void_t*)(lds + b * N + c * 256);
+      const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_void_t*)(buf + c * 256);
       asm volatile(
           "s_mov_b32 m0, %0\n\t"
           "global_load_lds_dwordx4 %1, off nt"
@@ -136,8 +135,34 @@ op_kernel(const FsTable tab) {
           : "memory", "m0");
     }
   };
-  issue_load(p_begin, 0);
-  if (NB == 2 && p_begin + 1 < p_end) issue_load(p_begin + 1, 1);
+  issue_load(p_begin);
+  // direct-to-LDS loads of a limb's tables, 1 KiB each: level-A operands and
+  // twist of both passes, post-twist (copies through registers, table after
+  // table, took 1 us each on a launch's first polynomial)
+  constexpr int kNt = kPbLds ? 20 : 12;
+  const uint32_t lane16 = 16 * lane;
+  auto issue_tables = [&](const unsigned char* base, const uint2* twist) {
+#pragma unroll
+    for (int k = 0; k < (kNt + W - 1) / W; ++k) {
+      const int ch = wave + k * W;
+      if (ch < kNt) {
+        const uint64_t at = ch < 4    ? ch * 1024
+                            : ch < 6  ? offsetof(PassTables, twist) + (ch - 4) * 1024
+                            : ch < 10 ? tab.tab_op + (ch - 6) * 1024
+                            : ch < 12 ? tab.tab_op + offsetof(PassTables, twist) + (ch - 10) * 1024
+                                      : tab.tab_op + offsetof(OnePassTables, post_b) + (ch - 12) * 1024;
+        const unsigned char* src =
+            twist && ch >= 10 && ch < 12 ? (const unsigned char*)twist + (ch - 10) * 1024 : base + at;
+        const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_void_t*)(buf + kTabOpA1 + ch * 256);
+        asm volatile(
+            "s_mov_b32 m0, %0\n\t"
+            "global_load_lds_dwordx4 %1, %2"
+            :
+            : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(lane16), "s"(src)
+            : "memory", "m0");
+      }
+    }
+  };
 
   // per-limb values in registers (the rest of the limb's tables is in LDS)
   const void* cur = nullptr;  // whose tables are staged: the limb's, with the unit's twist if it has one
@@ -148,58 +173,38 @@ op_kernel(const FsTable tab) {
   // consecutive steps of a wave (the factor is geometric in the step index)
   uint32_t pa0[4], pad[4];
 
-  uint32_t n = 0;
-  for (uint32_t p = p_begin; p < p_end; ++p, ++n) {
-    const int b = NB == 2 ? (int)(n & 1) : 0;
-    uint32_t* const buf = lds + b * N;
+  for (uint32_t p = p_begin; p < p_end; ++p) {
     const Item it = locate(tab, p, kc);
-    // this polynomial's loads: issued after them are, in order, the stores
-    // of p - 2, the loads of p + 1 and the stores of p - 1 (double buffer),
-    // or nothing (single buffer)
-    if (NB == 2) {
-      const int after = (n >= 2 ? CH : 0) + (p + 1 < p_end ? CH : 0) + (n >= 1 ? CH : 0);
-      if (after >= 3 * CH) wait_vmcnt<3 * CH>();
-      else if (after >= 2 * CH) wait_vmcnt<2 * CH>();
-      else if (after >= CH) wait_vmcnt<CH>();
-      else wait_vmcnt<0>();
-    } else {
-      wait_vmcnt<0>();  // the loads were issued last
-    }
     const FourStepLimb* limb = tab.u[it.unit].limbs + it.limb;
     const uint2* const twist = kInv ? tab.u[it.unit].twist : nullptr;
     const void* const key = twist ? (const void*)(twist + it.limb * 256) : limb;
     if (key != cur) {
       // rare (a few times per workgroup), and every wave is past the
-      // previous polynomial's last barrier, so the staged tables are free:
-      // copy the new limb's into LDS (waiting here keeps the pipeline free
-      // of waits on these loads)
+      // previous polynomial's last barrier, so the staged tables are free
       const auto* L = (const_as FourStepLimb*)limb;
-      const PassTables* T1 = L->pass1;
-      const OnePassTables* O = L->op;
+      const unsigned char* const base = tab.u[it.unit].tables + it.limb * tab.tab_stride;
+      const OnePassTables* O = (const OnePassTables*)(base + tab.tab_op);
+      issue_tables(base, twist ? twist + it.limb * 256 : nullptr);
       R = make_red(L->q, L->qneg);
-      const uint32_t* srcs[5] = {&T1->opA[0][0][0], (const uint32_t*)&T1->twist[0][0], &O->p2.opA[0][0][0],
-                                 (const uint32_t*)(twist ? twist + it.limb * 256 : &O->p2.twist[0][0]), (const uint32_t*)&O->post_b[0][0][0][0]};
-      const int offs[5] = {kTabOpA1, kTabTw1, kTabOpA2, kTabTw2, kTabPb};
-      const int lens[5] = {1024, 512, 1024, 512, 2048};
       pb_src = &O->post_b[0][0][0][0];
-#pragma unroll
-      for (int k = 0; k < (kPbLds ? 5 : 4); ++k)
-        for (int i = 4 * tid; i < lens[k]; i += 4 * 64 * W)
-          *(uint4*)(lds + offs[k] + i) = *(const uint4*)(srcs[k] + i);
+      const v4u a0 = *(const v4u*)&O->post_a[wave][lane][0], ad = *(const v4u*)&O->post_a[St1 > 1 ? W : wave][lane][0];
+      const auto* b1 = (const_as uint32_t*)(base + offsetof(PassTables, lb));
+      const auto* b2 = (const_as uint32_t*)((const unsigned char*)O + offsetof(PassTables, lb));
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        if (kR1 < 16) lb1[j] = T1->lb[j];
-
-        pa0[j] = O->post_a[wave][lane][j];
-        pad[j] = St1 > 1 ? O->post_a[W][lane][j] : 0u;
+        if (kR1 < 16) lb1[j] = make_uint2(b1[2 * j], b1[2 * j + 1]);
+        pa0[j] = a0[j];
+        pad[j] = ad[j];
       }
       if (kR2 < 16) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) lb2[i] = O->p2.lb[i];
+        for (int i = 0; i < 16; ++i) lb2[i] = make_uint2(b2[2 * i], b2[2 * i + 1]);
       }
-      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
       cur = key;
     }
+    // this wave's loads of the polynomial and of the tables (the builtin tells
+    // the compiler as well)
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     lds_barrier();  // the polynomial is in LDS (every wave's loads landed)
 
     const uint32_t q = R.q;
@@ -215,11 +220,11 @@ op_kernel(const FsTable tab) {
       uint2 tw1[4], pb[4][4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        opA1[j] = *(const v4i*)(lds + kTabOpA1 + (j * 64 + lane) * 4);
-        tw1[j] = *(const uint2*)(lds + kTabTw1 + (lane * 4 + j) * 2);
+        opA1[j] = *(const v4i*)(buf + kTabOpA1 + (j * 64 + lane) * 4);
+        tw1[j] = *(const uint2*)(buf + kTabTw1 + (lane * 4 + j) * 2);
 #pragma unroll
         for (int sg = 0; sg < 4; ++sg)
-          pb[j][sg] = kPbLds ? *(const uint2*)(lds + kTabPb + (((sg * 2 + j / 2) * 64 + lane) * 2 + j % 2) * 2)
+          pb[j][sg] = kPbLds ? *(const uint2*)(buf + kTabPb + (((sg * 2 + j / 2) * 64 + lane) * 2 + j % 2) * 2)
                              : pb_src[((sg * 2 + j / 2) * 64 + lane) * 2 + j % 2];
       }
       uint32_t pa[4] = {pa0[0], pa0[1], pa0[2], pa0[3]};
@@ -303,8 +308,8 @@ op_kernel(const FsTable tab) {
       uint2 tw2[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        opA2[j] = *(const v4i*)(lds + kTabOpA2 + (j * 64 + lane) * 4);
-        tw2[j] = *(const uint2*)(lds + kTabTw2 + (lane * 4 + j) * 2);
+        opA2[j] = *(const v4i*)(buf + kTabOpA2 + (j * 64 + lane) * 4);
+        tw2[j] = *(const uint2*)(buf + kTabTw2 + (lane * 4 + j) * 2);
       }
       uint2 rj[4], pf[4];  // level-B multipliers; factor of output t (lb2[8 + t])
       if (kR2 < 16) {
@@ -379,37 +384,18 @@ op_kernel(const FsTable tab) {
     }
     lds_barrier();
 
-    // ---- store: natural order, whole 1 KiB chunks per instruction.  With
-    // two buffers the wave reads all its chunks, and once every wave has
-    // (barrier) the buffer takes the polynomial after next while the stores
-    // drain; with one buffer the chunks are stored as they are read and the
-    // next polynomial is loaded after the barrier.
+    // ---- store: natural order, whole 1 KiB chunks per instruction; the next
+    // polynomial is loaded once every wave has read its chunks
     const int al = opaque(lane);
     uint32_t* const dst = tab.u[it.unit].out + it.poly_base;
-    if (NB == 2) {
-      uint4 outq[CH];
 #pragma unroll
-      for (int k = 0; k < CH; ++k) {
-        const uint32_t c = wave + k * W;
-        outq[k] = *(const uint4*)(buf + sw_out<C::out_a, C::out_b, C::out_sh>(c * 256 + 4 * al));
-      }
-      lds_barrier();  // every wave has read the buffer: it may be refilled
-      if (p + NB < p_end) issue_load(p + NB, b);
-#pragma unroll
-      for (int k = 0; k < CH; ++k) {
-        const uint32_t c = wave + k * W;
-        __builtin_nontemporal_store(*(const v4u*)&outq[k], (v4u*)(dst + c * 256 + 4 * al));
-      }
-    } else {
-#pragma unroll
-      for (int k = 0; k < CH; ++k) {
-        const uint32_t c = wave + k * W;
-        const uint4 v = *(const uint4*)(buf + sw_out<C::out_a, C::out_b, C::out_sh>(c * 256 + 4 * al));
-        __builtin_nontemporal_store(*(const v4u*)&v, (v4u*)(dst + c * 256 + 4 * al));
-      }
-      lds_barrier();
-      if (p + 1 < p_end) issue_load(p + 1, 0);
+    for (int k = 0; k < CH; ++k) {
+      const uint32_t c = wave + k * W;
+      const uint4 v = *(const uint4*)(buf + sw_out<C::out_a, C::out_b, C::out_sh>(c * 256 + 4 * al));
+      __builtin_nontemporal_store(*(const v4u*)&v, (v4u*)(dst + c * 256 + 4 * al));
     }
+    lds_barrier();
+    if (p + 1 < p_end) issue_load(p + 1);
   }
 }
 
