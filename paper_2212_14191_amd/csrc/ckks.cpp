@@ -947,11 +947,8 @@ tfhe_status tfhe_cmult(tfhe_ckks_ctx ctx, const uint32_t* ct, const uint32_t* pt
   tfhe_status st = check_ct_call(ctx, level, batch, nullptr, 0, false);
   if (st != TFHE_OK || batch == 0) return st;
   if (!al16(ct) || !al16(pt) || !al16(ct_out)) return fail(TFHE_EINVAL, "cmult: null or unaligned pointer");
-  const uint64_t plane = (uint64_t)level * batch * ctx->n;
-  hipStream_t s = (hipStream_t)stream;
-  hipError_t e = ew_launch(EW_MUL, ctx->plan->d_mod, ct, pt, ct_out, level, batch, ctx->n, s);
-  if (e == hipSuccess) e = ew_launch(EW_MUL, ctx->plan->d_mod, ct + plane, pt, ct_out + plane, level, batch, ctx->n, s);
-  return hip_check(e, "cmult");
+  return hip_check(ew_launch(EW_CT_MUL, ctx->plan->d_mod, ct, pt, ct_out, level, batch, ctx->n, (hipStream_t)stream),
+                   "cmult");
 }
 
 tfhe_status tfhe_hadd(tfhe_ckks_ctx ctx, const uint32_t* ct_a, const uint32_t* ct_b, uint32_t* ct_out,
@@ -959,12 +956,8 @@ tfhe_status tfhe_hadd(tfhe_ckks_ctx ctx, const uint32_t* ct_a, const uint32_t* c
   tfhe_status st = check_ct_call(ctx, level, batch, nullptr, 0, false);
   if (st != TFHE_OK || batch == 0) return st;
   if (!al16(ct_a) || !al16(ct_b) || !al16(ct_out)) return fail(TFHE_EINVAL, "hadd: null or unaligned pointer");
-  const uint64_t plane = (uint64_t)level * batch * ctx->n;
-  hipStream_t s = (hipStream_t)stream;
-  hipError_t e = ew_launch(EW_ADD, ctx->plan->d_mod, ct_a, ct_b, ct_out, level, batch, ctx->n, s);
-  if (e == hipSuccess)
-    e = ew_launch(EW_ADD, ctx->plan->d_mod, ct_a + plane, ct_b + plane, ct_out + plane, level, batch, ctx->n, s);
-  return hip_check(e, "hadd");
+  return hip_check(ew_launch(EW_CT_ADD, ctx->plan->d_mod, ct_a, ct_b, ct_out, 2 * level, batch, ctx->n,
+                             (hipStream_t)stream), "hadd");
 }
 
 }  // extern "C"

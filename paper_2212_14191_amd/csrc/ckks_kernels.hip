@@ -33,9 +33,10 @@ __global__ void __launch_bounds__(kThreads)
 tensor_kernel(const uint4* __restrict__ a, const uint4* __restrict__ b, uint4* out,
               uint4* __restrict__ d2, const ModConst* __restrict__ mods, uint64_t plane4,
               uint64_t per_limb4) {
-  for (uint64_t i = blockIdx.x * (uint64_t)kThreads + threadIdx.x; i < plane4;
-       i += (uint64_t)gridDim.x * kThreads) {
-    const ModConst m = mods[i / per_limb4];
+  const ModConst m = mods[blockIdx.y];  // one limb: scalar constants
+  for (uint64_t k = blockIdx.x * (uint64_t)kThreads + threadIdx.x; k < per_limb4;
+       k += (uint64_t)gridDim.x * kThreads) {
+    const uint64_t i = blockIdx.y * per_limb4 + k;
     const uint4 c0 = a[i], c1 = a[plane4 + i], e0 = b[i], e1 = b[plane4 + i];
     d2[i] = map4(c1, [&](uint32_t x, int k) { return mul_mod(x, comp(e1, k), m); });
     out[i] = map4(c0, [&](uint32_t x, int k) { return mul_mod(x, comp(e0, k), m); });
@@ -492,7 +493,7 @@ hipError_t launch_tensor(const uint32_t* a, const uint32_t* b, uint32_t* out, ui
                          const ModConst* mods, uint32_t level, uint32_t batch, uint32_t n,
                          hipStream_t s) {
   const uint64_t per_limb4 = (uint64_t)batch * n / 4, plane4 = per_limb4 * level;
-  TFHE_TIMED(K_TENSOR, s, hipLaunchKernelGGL(tensor_kernel, dim3(grid_for(plane4)), dim3(kThreads), 0, s,
+  TFHE_TIMED(K_TENSOR, s, hipLaunchKernelGGL(tensor_kernel, dim3(grid_for(per_limb4), level), dim3(kThreads), 0, s,
                                              (const uint4*)a, (const uint4*)b, (uint4*)out, (uint4*)d2,
                                              mods, plane4, per_limb4));
   return hipGetLastError();

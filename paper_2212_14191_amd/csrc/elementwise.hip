@@ -9,27 +9,38 @@ namespace {
 constexpr int kThreads = 256;
 
 template <int kOp>
+__device__ __forceinline__ uint4 ew(uint4 x, uint4 y, const ModConst& m) {
+  if (kOp == EW_ADD || kOp == EW_CT_ADD)
+    return make_uint4(add_mod(x.x, y.x, m.q), add_mod(x.y, y.y, m.q), add_mod(x.z, y.z, m.q), add_mod(x.w, y.w, m.q));
+  if (kOp == EW_SUB)
+    return make_uint4(sub_mod(x.x, y.x, m.q), sub_mod(x.y, y.y, m.q), sub_mod(x.z, y.z, m.q), sub_mod(x.w, y.w, m.q));
+  return make_uint4(mul_mod(x.x, y.x, m), mul_mod(x.y, y.y, m), mul_mod(x.z, y.z, m), mul_mod(x.w, y.w, m));
+}
+
+// blockIdx.y is the limb, so that its constants are scalar (an index over all
+// limbs took a 64-bit division per 16 bytes).  A ciphertext op does both
+// components of a position: one launch, and CMULT reads its plaintext once.
+// Bound by HBM; CMULT then HADD of 32 ciphertexts, N = 2^15, level 12: 99 ->
+// 88 us (6.2 TB/s, part of it the last-level cache's).  Streaming hints on the
+// loads or stores are slower (89-92 us).
+template <int kOp>
 __global__ void __launch_bounds__(kThreads)
 ew_kernel(const ModConst* __restrict__ mods, const uint4* __restrict__ a, const uint4* __restrict__ b,
-          uint4* __restrict__ c, uint64_t total4, uint64_t per_limb4, uint32_t n4) {
-  for (uint64_t i = blockIdx.x * (uint64_t)kThreads + threadIdx.x; i < total4;
-       i += (uint64_t)gridDim.x * kThreads) {
-    const uint32_t limb = (uint32_t)(i / per_limb4);
-    const ModConst m = mods[limb];
-    const uint4 x = a[i];
-    const uint4 y = kOp == EW_MUL_BCAST ? b[(uint64_t)limb * n4 + (i % n4)] : b[i];
-    uint4 z;
-    if (kOp == EW_MUL || kOp == EW_MUL_BCAST) {
-      z.x = mul_mod(x.x, y.x, m); z.y = mul_mod(x.y, y.y, m);
-      z.z = mul_mod(x.z, y.z, m); z.w = mul_mod(x.w, y.w, m);
-    } else if (kOp == EW_ADD) {
-      z.x = add_mod(x.x, y.x, m.q); z.y = add_mod(x.y, y.y, m.q);
-      z.z = add_mod(x.z, y.z, m.q); z.w = add_mod(x.w, y.w, m.q);
+          uint4* __restrict__ c, uint64_t plane4, uint64_t per_limb4, uint32_t n4) {
+  constexpr bool kPair = kOp == EW_CT_MUL || kOp == EW_CT_ADD;
+  const uint32_t limb = blockIdx.y;
+  const ModConst m = mods[limb];
+  const uint64_t base = limb * per_limb4, step = (uint64_t)gridDim.x * kThreads;
+  for (uint64_t k = blockIdx.x * (uint64_t)kThreads + threadIdx.x; k < per_limb4; k += step) {
+    const uint64_t i = base + k;
+    const uint4 y = b[kOp == EW_MUL_BCAST ? (uint64_t)limb * n4 + (k & (n4 - 1)) : i], x = a[i];
+    if (kPair) {
+      const uint4 x1 = a[plane4 + i], y1 = kOp == EW_CT_ADD ? b[plane4 + i] : y;
+      c[i] = ew<kOp>(x, y, m);
+      c[plane4 + i] = ew<kOp>(x1, y1, m);
     } else {
-      z.x = sub_mod(x.x, y.x, m.q); z.y = sub_mod(x.y, y.y, m.q);
-      z.z = sub_mod(x.z, y.z, m.q); z.w = sub_mod(x.w, y.w, m.q);
+      c[i] = ew<kOp>(x, y, m);
     }
-    c[i] = z;
   }
 }
 
@@ -69,25 +80,24 @@ uint32_t grid_for(uint64_t items) {
 
 hipError_t ew_launch(EwOp op, const ModConst* mods, const uint32_t* a, const uint32_t* b,
                      uint32_t* c, uint32_t limb_count, uint32_t batch, uint32_t n, hipStream_t s) {
-  const uint64_t total4 = (uint64_t)limb_count * batch * n / 4;
+  if (op == EW_CT_ADD) limb_count /= 2;
   const uint64_t per_limb4 = (uint64_t)batch * n / 4;
-  const uint32_t n4 = n / 4;
-  const uint32_t grid = grid_for(total4);
+  if (limb_count == 0 || per_limb4 == 0) return hipSuccess;
+  if (limb_count > 65535) return hipErrorInvalidValue;
+  const dim3 grid(grid_for(per_limb4), limb_count);
+  const uint64_t plane4 = limb_count * per_limb4;
   const uint4 *A = (const uint4*)a, *B = (const uint4*)b;
   uint4* C = (uint4*)c;
+  auto run = [&](auto kernel) {
+    TFHE_TIMED(K_EW, s, hipLaunchKernelGGL(kernel, grid, dim3(kThreads), 0, s, mods, A, B, C, plane4, per_limb4, n / 4));
+  };
   switch (op) {
-    case EW_MUL:
-      TFHE_TIMED(K_EW, s, hipLaunchKernelGGL(ew_kernel<EW_MUL>, dim3(grid), dim3(kThreads), 0, s, mods, A, B, C, total4, per_limb4, n4));
-      break;
-    case EW_ADD:
-      TFHE_TIMED(K_EW, s, hipLaunchKernelGGL(ew_kernel<EW_ADD>, dim3(grid), dim3(kThreads), 0, s, mods, A, B, C, total4, per_limb4, n4));
-      break;
-    case EW_SUB:
-      TFHE_TIMED(K_EW, s, hipLaunchKernelGGL(ew_kernel<EW_SUB>, dim3(grid), dim3(kThreads), 0, s, mods, A, B, C, total4, per_limb4, n4));
-      break;
-    case EW_MUL_BCAST:
-      TFHE_TIMED(K_EW, s, hipLaunchKernelGGL(ew_kernel<EW_MUL_BCAST>, dim3(grid), dim3(kThreads), 0, s, mods, A, B, C, total4, per_limb4, n4));
-      break;
+    case EW_MUL: run(ew_kernel<EW_MUL>); break;
+    case EW_ADD: run(ew_kernel<EW_ADD>); break;
+    case EW_SUB: run(ew_kernel<EW_SUB>); break;
+    case EW_MUL_BCAST: run(ew_kernel<EW_MUL_BCAST>); break;
+    case EW_CT_MUL: run(ew_kernel<EW_CT_MUL>); break;
+    case EW_CT_ADD: run(ew_kernel<EW_CT_ADD>); break;
   }
   return hipGetLastError();
 }

@@ -198,7 +198,10 @@ hipError_t co_transform(const tfhe_ntt_plan_s* p, bool inverse, const uint32_t* 
                         hipStream_t s);
 
 // ---- element-wise launchers (elementwise.hip)
-enum EwOp { EW_MUL = 0, EW_ADD = 1, EW_SUB = 2, EW_MUL_BCAST = 3 };
+// The ciphertext ops take both components of a and c, one after the other:
+// EW_CT_MUL by one plaintext b [limb_count][batch][N]; EW_CT_ADD with a second
+// ciphertext b, limb_count counting the limbs of both components.
+enum EwOp { EW_MUL = 0, EW_ADD = 1, EW_SUB = 2, EW_MUL_BCAST = 3, EW_CT_MUL = 4, EW_CT_ADD = 5 };
 hipError_t ew_launch(EwOp op, const ModConst* mods, const uint32_t* a, const uint32_t* b,
                      uint32_t* c, uint32_t limb_count, uint32_t batch, uint32_t n, hipStream_t s);
 hipError_t frobenius_launch(const uint32_t* in, uint32_t* out, uint32_t galois, uint32_t rows,
