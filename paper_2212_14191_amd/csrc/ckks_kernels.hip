@@ -7,6 +7,7 @@
 #include <algorithm>
 
 #include "ckks_internal.hpp"
+#include "frobenius_dev.hpp"
 
 namespace tfhe {
 namespace {
@@ -310,6 +311,16 @@ conv_mfma_kernel(const ConvSet set) {
   }
 }
 
+// The same with a workgroup per polynomial (row of component blockIdx.y).
+template <int kLogN>
+__global__ void __launch_bounds__(FrobShape<kLogN>::threads)
+frobenius_pair_poly(const uint32_t* in0, uint32_t* out0, const uint32_t* in1, uint32_t* out1, const GaloisSet gs) {
+  __shared__ __attribute__((aligned(16))) uint32_t lds[FrobShape<kLogN>::words];
+  const uint64_t at = (uint64_t)blockIdx.x << kLogN;
+  const bool second = blockIdx.y != 0;
+  frob_poly<kLogN>((second ? in1 : in0) + at, (second ? out1 : out0) + at, gs.g[blockIdx.x % gs.batch], lds);
+}
+
 // FrobeniusMap out_j = in_{pi(j)} of two arrays in one launch (the two
 // components of a ciphertext), with the Galois element of each row's batch
 // element.
@@ -372,6 +383,19 @@ frobenius_multi_kernel(const CtDescSet set, uint32_t log_n) {
     const uint64_t o = (((uint64_t)limb * c.B + c.idx) << log_n) + j;
     (second ? c.d : c.out)[o] = c.a[(second ? per : 0) + ((uint64_t)limb << log_n) + src];
   }
+}
+
+// The same with a workgroup per polynomial (component blockIdx.x % 2 of limb
+// blockIdx.x / 2).
+template <int kLogN>
+__global__ void __launch_bounds__(FrobShape<kLogN>::threads)
+frobenius_multi_poly(const CtDescSet set) {
+  __shared__ __attribute__((aligned(16))) uint32_t lds[FrobShape<kLogN>::words];
+  const CtDesc& c = set.c[blockIdx.y];
+  const uint32_t limb = blockIdx.x / 2, second = blockIdx.x % 2;
+  if (limb >= c.level) return;
+  frob_poly<kLogN>(c.a + ((uint64_t)(second ? c.level : 0) + limb) * (1u << kLogN),
+                   (second ? c.d : c.out) + (((uint64_t)limb * c.B + c.idx) << kLogN), c.galois, lds);
 }
 
 // Copies each ciphertext of a mixed-level batch out of its level group's
@@ -445,6 +469,14 @@ hipError_t ConvQueue::flush(uint32_t num_cus, KernelId id, hipStream_t s) {
 hipError_t launch_frobenius_pair(const uint32_t* in0, uint32_t* out0, const uint32_t* in1, uint32_t* out1,
                                  const GaloisSet& gs, uint32_t rows, uint32_t log_n, hipStream_t s) {
   const uint64_t per = (uint64_t)rows << log_n;
+  if (frob_by_poly(log_n, 2ull * rows)) {
+    frob_switch(log_n, [&](auto ln) {
+      constexpr int kLogN = decltype(ln)::value;
+      TFHE_TIMED(K_FROB, s, hipLaunchKernelGGL(frobenius_pair_poly<kLogN>, dim3(rows, 2),
+                                               dim3(FrobShape<kLogN>::threads), 0, s, in0, out0, in1, out1, gs));
+    });
+    return hipGetLastError();
+  }
   TFHE_TIMED(K_FROB, s, hipLaunchKernelGGL(frobenius_pair_kernel, dim3(grid_for(2 * per)), dim3(kThreads), 0, s,
                                            in0, out0, in1, out1, gs, per, log_n));
   return hipGetLastError();
@@ -466,6 +498,20 @@ hipError_t launch_tensor_multi(const CtDescSet& set, const ModConst* mods, uint3
 
 hipError_t launch_frobenius_multi(const CtDescSet& set, uint32_t log_n, hipStream_t s) {
   if (set.count == 0) return hipSuccess;
+  uint32_t most = 0;
+  uint64_t polys = 0;
+  for (uint32_t r = 0; r < set.count; ++r) {
+    most = std::max(most, set.c[r].level);
+    polys += 2ull * set.c[r].level;
+  }
+  if (frob_by_poly(log_n, polys)) {
+    frob_switch(log_n, [&](auto ln) {
+      constexpr int kLogN = decltype(ln)::value;
+      TFHE_TIMED(K_FROB, s, hipLaunchKernelGGL(frobenius_multi_poly<kLogN>, dim3(2 * most, set.count),
+                                               dim3(FrobShape<kLogN>::threads), 0, s, set));
+    });
+    return hipGetLastError();
+  }
   TFHE_TIMED(K_FROB, s, hipLaunchKernelGGL(frobenius_multi_kernel, dim3(multi_grid(set, 2u << log_n), set.count),
                                            dim3(kThreads), 0, s, set, log_n));
   return hipGetLastError();

@@ -1,7 +1,7 @@
 // Element-wise kernels of the hierarchical reconstruction (Sec. IV-A,
 // Table 2): Hada-Mult, Ele-Add, Ele-Sub and FrobeniusMap, over the
 // (limb, batch, N) layout.  All are HBM-bound: 16-byte accesses, one pass.
-#include "internal.hpp"
+#include "frobenius_dev.hpp"
 
 namespace tfhe {
 namespace {
@@ -55,6 +55,15 @@ frobenius_kernel(const uint32_t* __restrict__ in, uint32_t* __restrict__ out, ui
     const uint32_t src = (((2 * j + 1) * galois) & mask2n) >> 1;
     out[i] = in[(i - j) + src];
   }
+}
+
+// The same with a workgroup per polynomial.
+template <int kLogN>
+__global__ void __launch_bounds__(FrobShape<kLogN>::threads)
+frobenius_poly(const uint32_t* in, uint32_t* out, uint32_t galois) {
+  __shared__ __attribute__((aligned(16))) uint32_t lds[FrobShape<kLogN>::words];
+  const uint64_t at = (uint64_t)blockIdx.x << kLogN;
+  frob_poly<kLogN>(in + at, out + at, galois, lds);
 }
 
 // out[l][b][i] = in[b][i] mod q_l for small signed integers in (-2^31, 2^31).
@@ -112,6 +121,14 @@ hipError_t load_small_launch(const ModConst* mods, const int32_t* in, uint32_t* 
 
 hipError_t frobenius_launch(const uint32_t* in, uint32_t* out, uint32_t galois, uint32_t rows,
                             uint32_t log_n, hipStream_t s) {
+  if (frob_by_poly(log_n, rows)) {
+    frob_switch(log_n, [&](auto ln) {
+      constexpr int kLogN = decltype(ln)::value;
+      TFHE_TIMED(K_FROB, s, hipLaunchKernelGGL(frobenius_poly<kLogN>, dim3(rows), dim3(FrobShape<kLogN>::threads), 0,
+                                               s, in, out, galois));
+    });
+    return hipGetLastError();
+  }
   const uint64_t total = (uint64_t)rows << log_n;
   TFHE_TIMED(K_FROB, s, hipLaunchKernelGGL(frobenius_kernel, dim3(grid_for(total)), dim3(kThreads), 0, s, in, out,
                      galois, total, log_n));
