@@ -463,38 +463,52 @@ void launch_pass_r(const tfhe_ntt_plan_s* p, uint32_t r, const FsTable& t, hipSt
 // q 2^32 and reduced once per output; every quantity is exact, so the
 // result equals the unfused sequence bit for bit.  Items of all level groups
 // form one sequence (group g from item0): one launch for a mixed-level batch.
-// Pipelining: the task's source (tile or d2) and its two key blocks arrive
-// by direct-to-LDS loads; the next task's source is issued into the other
-// buffer as soon as this task's has landed, so one load is always in flight
-// behind the arithmetic.  Keys and d2 are loaded into each wave's own slots
-// of the output layout (slot (4 wave + j, lane) = natural positions st_off).
-// Items are the wide ones of the 256-point stage (8 waves, 32 vectors: every
-// load and store a whole 128-byte line, 144 KiB of LDS, one workgroup per
-// CU) wherever N >= 2^13, else the narrow ones (4 waves, 16 vectors, two
-// workgroups per CU); wide measured 2 % faster for this kernel at 2^16.
-template <bool kWide>
-__global__ void __launch_bounds__(kWide ? 512 : 256, kWide ? 1 : 2)
+// The products are formed in the matrix cores' result layout, with the keys
+// read from natural-order LDS tiles at the results' positions; only an item's
+// sums go through LDS into natural order for whole-line stores.
+// A wave takes two vectors of the 256-point stage (512 words) and eight or
+// sixteen of them share an item.  Sources arrive by direct-to-LDS loads, one
+// task ahead.  The keys either
+//   stream: each task's two blocks arrive with its source (wide items, 32
+//     vectors, 144 KiB of LDS; narrow ones, 64 KiB, below N = 2^13 or where all
+//     narrow items run at once), or
+//   stay: the blocks of all (up to kKeepDigits) digits are resident while a
+//     workgroup walks the batch elements of one position and column block
+//     (narrow items, 144 KiB).
+// Bound by memory, HBM and the L2's delivery of the keys (without the
+// arithmetic the streaming kernel takes as long).  64 pairs at N = 2^16, level
+// 24, three digits: 0.98 ms with the products in natural order (each task's
+// results through LDS, three barriers), 0.91 streamed, 0.77 resident, against
+// 0.61 for the HBM bytes at the copy rate.
+constexpr int kKeepDigits = 3;
+template <bool kWide, bool kKeep>
+__global__ void __launch_bounds__((2 * Geo<false, 16, kWide>::threads), (kKeep ? 2 : 4))
 ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst* __restrict__ mods,
-        uint32_t log_n, uint32_t ipp_log, uint32_t alpha_inv, uint32_t items) {
+        const unsigned char* __restrict__ tables, uint64_t tab_stride, uint32_t log_n, uint32_t ipp_log,
+        uint32_t alpha_inv, uint32_t items, uint32_t share, uint32_t extra) {
   using G = Geo<false, 16, kWide>;
-  // two source buffers, then the key blocks of components 0 and 1
-  __shared__ __attribute__((aligned(16))) uint32_t lds[4 * G::tile];
-  uint32_t* const kbuf = lds + 2 * G::tile;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  static_assert(!kWide || !kKeep, "resident keys: narrow items");
+  constexpr int kSets = 2;  // vectors per wave
+  typedef uint32_t vset __attribute__((ext_vector_type(kSets)));
+  // two source buffers, (resident keys: the output stage of component 1,) the
+  // key blocks of components 0 and 1 (of every digit)
+  constexpr int kKeys = (kKeep ? 3 : 2) * G::tile, kKeyTiles = kKeep ? 2 * kKeepDigits : 2;
+  __shared__ __attribute__((aligned(16))) uint32_t lds[kKeys + kKeyTiles * G::tile];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int quad = wave * kSets / 4, first = wave * kSets % 4;  // this wave's vectors: 4 quad + first ..
   const int i16 = lane & 15, g = lane >> 4;
   const uint64_t N = 1ull << log_n;
   const uint32_t S = (uint32_t)(N >> 8);  // second-pass columns (rows of the first)
   const uint64_t kplane = (uint64_t)(set.L + set.K) * N;  // one key component
-  // per-lane offsets within a polynomial for column block blk
-  auto offsets = [&](uint32_t blk, uint32_t* ld, uint32_t* st) {
-    const uint32_t c0 = blk * G::W;
+  // this lane's byte offsets within a polynomial for the wave's slabs kSets wave ..
+  // (natural order; tiled): column block blk adds blk W words and blk W P words
+  uint32_t st[kSets], ld[kSets];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t row = G::Rs * (4 * wave + j) + lane % G::Rs, col = 4 * (lane / G::Rs);
-      st[j] = row * S + c0 + col;
-      ld[j] = ((c0 + col) >> 4) * (16 * G::P) + 16 * row + (col & 15);
-    }
-  };
+  for (int j = 0; j < kSets; ++j) {
+    const uint32_t row = G::Rs * (kSets * wave + j) + lane % G::Rs, col = 4 * (lane / G::Rs);
+    st[j] = 4 * (row * S + col);
+    ld[j] = 4 * ((col >> 4) * (16 * G::P) + 16 * row + (col & 15));
+  }
   struct Pos {
     uint32_t grp, b, blk, t, pl, own;
   };
@@ -507,75 +521,104 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
     const uint32_t tb = div_by(l, Gr.batch, Gr.batch_inv);
     p.b = l - tb * Gr.batch;
     p.blk = tb & ((1u << ipp_log) - 1);
+    if (kKeep) p.blk = 2 * p.blk + blockIdx.x / 8 % 2;
     p.t = tb >> ipp_log;
     p.pl = p.t < Gr.level ? p.t : set.L + (p.t - Gr.level);  // plan limb
     p.own = p.t < Gr.level ? div_by(p.t, set.alpha, alpha_inv) : 0xFFFFFFFFu;
     return p;
   };
-  // 16 bytes per lane into this wave's slot (4 wave + j) of `dst` (output layout)
-  auto load_slots = [&](const uint32_t* src, const uint32_t* st, uint32_t* dst) {
+  // 16 bytes per lane into this wave's slabs of the tile at LDS word `dst`
+  auto load_slabs = [&](const uint32_t* from, const uint32_t* off, int dst, auto nt) {
+    const uint64_t at = (uint64_t)from;
+    const uint64_t src = (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(at >> 32)) << 32 |
+                         (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)at);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_void_t*)(dst + (4 * wave + j) * G::pitch);
-      asm volatile(
-          "s_mov_b32 m0, %0\n\t"
-          "global_load_lds_dwordx4 %1, off"
-          :
-          : "s"(__builtin_amdgcn_readfirstlane(lds_addr)), "v"(src + st[j])
-          : "memory", "m0");
+    for (int j = 0; j < kSets; ++j) {
+      const uint32_t lds_addr = (uint32_t)(uintptr_t)(lds_void_t*)(lds + dst + (kSets * wave + j) * G::pitch);
+      if (decltype(nt)::value)
+        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                     :
+                     : "s"(lds_addr), "v"(off[j]), "s"(src)
+                     : "memory", "m0");
+      else
+        asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :
+                     : "s"(lds_addr), "v"(off[j]), "s"(src)
+                     : "memory", "m0");
     }
   };
-  // the source of task (position p, digit jd) into buffer buf: 4 loads per lane
+  // the source of task (position p, digit jd) into buffer buf
   auto issue_source = [&](const Pos& p, uint32_t jd, int buf) {
     const IpGroup& Gr = set.g[p.grp];
     const uint32_t ext = Gr.level + set.K;
-    uint32_t ld[4], st[4];
-    offsets(p.blk, ld, st);
     if (jd == p.own)
-      load_slots(Gr.d2 + ((uint64_t)p.t * Gr.batch + p.b) * N, st, lds + buf * G::tile);
+      load_slabs(Gr.d2 + ((uint64_t)(p.t * Gr.batch + p.b) << log_n) + p.blk * G::W, st, buf * G::tile, std::false_type{});
     else
-      issue_tile<G::pitch>(Gr.src + ((uint64_t)(jd * ext + p.t) * Gr.batch + p.b) * N, ld, lds + buf * G::tile,
-                           wave);
+      load_slabs(Gr.src + ((uint64_t)((jd * ext + p.t) * Gr.batch + p.b) << log_n) + p.blk * (G::W * G::P), ld,
+                 buf * G::tile, std::true_type{});
   };
 
   touch(set.count, set.g[0].src, set.g[0].batch_inv, set.keys.k[0], limbs, items);
-  uint32_t w = blockIdx.x, jd = 0;
-  if (w >= items) return;
+  // Streamed keys: item w, then one per grid.  Resident keys: a pair of
+  // workgroups on one XCD (8 apart) walks a contiguous range of block pairs,
+  // batch element by element, each with one block of the pair (the halves of a
+  // 128-byte line).
+  uint32_t w = blockIdx.x, jd = 0, end = items, step = gridDim.x;
+  if (kKeep) {
+    const uint32_t slot = blockIdx.x / 16 * 8 + blockIdx.x % 8;
+    w = slot * share + min(slot, extra);
+    end = (slot + 1) * share + min(slot + 1, extra);
+    step = 1;
+  }
+  if (w >= end) return;
   Pos p = pos_of(w);
 
-  const FourStepLimb* cur = nullptr;
-  v4i opA[4], opB[4];
+  uint32_t cur = 0xFFFFFFFFu;  // the plan limb whose tables are loaded
+  uint32_t kept = 0, digits = 0;  // the block of limb cur whose keys are resident, and of how many digits
+  v4i opA[4];
   uint2 tw[4];
   Red R{};
   uint32_t m_r = 0, m_rp = 0;  // 2^32 mod q and its companion
-  uint64_t s0[4][4], s1[4][4];  // sums of products, kept below q 2^32
+  uint64_t s0[4][kSets], s1[4][kSets];  // sums of products, kept below q 2^32
   issue_source(p, 0, 0);
-  bool stored_after = false;  // the previous task ended its item (8 stores after this source)
+  bool stored_after = false;  // the previous task ended its item (2 kSets stores after this source)
   for (int cb = 0;; cb ^= 1) {
     uint32_t* const src = lds + cb * G::tile;
     const IpGroup& Gr = set.g[p.grp];
     // the task after this one: the next digit, else the next item
     uint32_t nw = w, njd = jd + 1;
     if (njd == Gr.digits) {
-      nw = w + gridDim.x;
+      nw = w + step;
       njd = 0;
     }
-    const bool next = nw < items;
-    uint32_t ld[4], st[4];
-    offsets(p.blk, ld, st);
-    if (jd == 0 && limbs + p.pl != cur) {
+    const bool next = nw < end;
+    // component c of digit d's key at this position, natural order
+    auto key_at = [&](uint32_t d, int c) {
+      return set.keys.k[set.keys.count == 1 ? 0 : Gr.key0 + p.b] + (2 * d + c) * kplane + ((uint64_t)p.pl << log_n) +
+             p.blk * G::W;
+    };
+    if (kKeep && (p.pl != cur || p.blk != kept || Gr.digits > digits)) {
+      // every wave is past the last item's barriers: nothing reads the keys
+      kept = p.blk;
+      digits = Gr.digits;
+      for (uint32_t d = 0; d < digits; ++d) {
+        load_slabs(key_at(d, 0), st, kKeys + 2 * d * G::tile, std::false_type{});
+        load_slabs(key_at(d, 1), st, kKeys + (2 * d + 1) * G::tile, std::false_type{});
+      }
+      stored_after = false;  // wait for all of it
+    }
+    if (p.pl != cur) {
       // rare: completed here, so that the pipeline carries no wait on these
-      cur = limbs + p.pl;
-      const auto* L = (const_as FourStepLimb*)cur;
+      cur = p.pl;
+      const auto* L = (const_as FourStepLimb*)(limbs + cur);
       R = make_red(L->q, L->qneg);
-      const auto* m = (const_as ModConst*)mods + p.pl;
+      const auto* m = (const_as ModConst*)(mods + cur);
       m_r = m->r;
       m_rp = m->rp;
-      const PassTables* P = L->pass2;
+      const PassTables* P = (const PassTables*)(tables + cur * tab_stride);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         opA[j] = *(const v4i*)&P->opA[j][lane][0];
-        opB[j] = *(const v4i*)&P->opB[j][lane][0];
         tw[j] = P->twist[lane][j];
       }
       // the builtin (unlike an asm wait) tells the compiler these registers
@@ -583,14 +626,15 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
       __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     }
     // this task's source: issued before the previous task's stores (if any)
-    if (stored_after) wait_vmcnt<8>();
+    if (stored_after) wait_vmcnt<2 * kSets>();
     else wait_vmcnt<0>();
     lds_barrier();  // the source is in LDS; every wave is done with the other buffer and the keys
     // this task's keys, then the next task's source
-    const uint32_t* key = set.keys.k[set.keys.count == 1 ? 0 : Gr.key0 + p.b];
-    const uint32_t* krow = key + (uint64_t)jd * 2 * kplane + (uint64_t)p.pl * N;
-    load_slots(krow, st, kbuf);
-    load_slots(krow + kplane, st, kbuf + G::tile);
+    const int kk = kKeep ? kKeys + 2 * (int)jd * G::tile : kKeys;
+    if (!kKeep) {
+      load_slabs(key_at(jd, 0), st, kKeys, std::false_type{});
+      load_slabs(key_at(jd, 1), st, kKeys + G::tile, std::false_type{});
+    }
     Pos np = p;
     if (next) {
       if (nw != w) np = pos_of(nw);
@@ -600,79 +644,69 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s0[j][e] = s1[j][e] = 0;
+        for (int e = 0; e < kSets; ++e) s0[j][e] = s1[j][e] = 0;
     }
     const uint32_t q = R.q;
+    // y at this lane's positions of the matrix cores' result layout: rows
+    // i16 + 16 (4 g + j), the wave's vectors
+    auto at = [&](int j) {
+      const int row = i16 + 16 * (4 * g + j);
+      return (row / G::Rs) * G::pitch + (quad * G::Rs + row % G::Rs) * 4 + first;
+    };
+    vset y[4];
     if (jd != p.own) {
-      uint4 rows[4];
+      vset rows[4];
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         const int row = 16 * (4 * g + c) + i16;
-        rows[c] = *(const uint4*)(src + (row / G::Rs) * G::pitch + (wave * G::Rs + row % G::Rs) * 4);
+        rows[c] = *(const vset*)(src + (row / G::Rs) * G::pitch + (quad * G::Rs + row % G::Rs) * 4 + first);
       }
-      uint4 res[4];
-      {
-        const v4i bias = {(int)q, (int)q, (int)q, (int)q};
-        const v4i zero = {0, 0, 0, 0};
+      const v4i bias = {(int)q, (int)q, (int)q, (int)q};
+      const v4i zero = {0, 0, 0, 0};
 #pragma unroll
-        for (int sg = 0; sg < 4; ++sg) {
-          v4i x;
+      for (int sg = 0; sg < kSets; ++sg) {
+        const v4i x = {(int)rows[0][sg], (int)rows[1][sg], (int)rows[2][sg], (int)rows[3][sg]};
+        const v4i a0 = mfma(x, opA[0], bias);
+        const v4i a1 = mfma(x, opA[1], zero);
+        const v4i a2 = mfma(x, opA[2], bias);
+        const v4i a3 = mfma(x, opA[3], zero);
+        v4i z;
 #pragma unroll
-          for (int c = 0; c < 4; ++c)
-            x[c] = (int)(sg == 0 ? rows[c].x : sg == 1 ? rows[c].y : sg == 2 ? rows[c].z : rows[c].w);
-          const v4i a0 = mfma(x, opA[0], bias);
-          const v4i a1 = mfma(x, opA[1], zero);
-          const v4i a2 = mfma(x, opA[2], bias);
-          const v4i a3 = mfma(x, opA[3], zero);
-          v4i z;
+        for (int j = 0; j < 4; ++j)
+          z[j] = (int)twist_digits(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw[j], R);
+        // level B: the same symmetric matrix (the twist carries its 2^32)
+        const v4i b0 = mfma(opA[0], z, bias);
+        const v4i b1 = mfma(opA[1], z, zero);
+        const v4i b2 = mfma(opA[2], z, bias);
+        const v4i b3 = mfma(opA[3], z, zero);
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            z[j] = (int)twist_digits(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw[j], R);
-          const v4i b0 = mfma(opB[0], z, bias);
-          const v4i b1 = mfma(opB[1], z, zero);
-          const v4i b2 = mfma(opB[2], z, bias);
-          const v4i b3 = mfma(opB[3], z, zero);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const uint32_t r = reduce_once(fuse_redc(b0[j], b1[j], b2[j], b3[j], R), q);
-            if (sg == 0) res[j].x = r;
-            else if (sg == 1) res[j].y = r;
-            else if (sg == 2) res[j].z = r;
-            else res[j].w = r;
-          }
-        }
+        for (int j = 0; j < 4; ++j) y[j][sg] = fuse_redc(b0[j], b1[j], b2[j], b3[j], R);
       }
-      lds_barrier();  // every wave has read the source
+    } else {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int row = i16 + 16 * (4 * g + j);
-        *(uint4*)(src + (row / G::Rs) * G::pitch + (wave * G::Rs + row % G::Rs) * 4) = res[j];
-      }
+      for (int j = 0; j < 4; ++j) y[j] = *(const vset*)(src + at(j));
     }
-    // the keys (issued before the next source) have landed; the results in
-    // the output layout are complete in every wave
-    if (next) wait_vmcnt<4>();
-    else wait_vmcnt<0>();
-    lds_barrier();
-    // s += y k as one 64-bit multiply-add; with y, k < q < 2^31 the sum
-    // stays below q 2^32 + q^2 < 2^64, and taking q off its high word when
-    // that reaches q keeps s below q 2^32.  Whole-vector 16-byte reads:
-    // through uint4 the compiler splits the key reads into dword pairs,
-    // which conflict four ways across the wave.
-    auto mac = [&](uint64_t* acc, const v4u& y, const v4u& kk) {
+    if (!kKeep) {
+      // the keys (issued before the next source) have landed, in every wave
+      if (next) wait_vmcnt<kSets>();
+      else wait_vmcnt<0>();
+      lds_barrier();
+    }
+    // s += y k as one 64-bit multiply-add; with y < q + 2^17 and k < q < 2^31
+    // the sum stays below q 2^32 + q^2 + 2^48 < 2^64, and taking q off its high
+    // word when that reaches q keeps s below q 2^32.
+    auto mac = [&](uint64_t* acc, const vset& v, const vset& key) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint64_t v = (uint64_t)y[e] * kk[e] + acc[e];
-        const uint32_t hi = (uint32_t)(v >> 32);
-        acc[e] = ((uint64_t)min(hi, hi - q) << 32) | (uint32_t)v;
+      for (int e = 0; e < kSets; ++e) {
+        const uint64_t sum = (uint64_t)v[e] * key[e] + acc[e];
+        const uint32_t hi = (uint32_t)(sum >> 32);
+        acc[e] = ((uint64_t)min(hi, hi - q) << 32) | (uint32_t)sum;
       }
     };
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      const int slot = (4 * wave + j) * G::pitch + lane * 4;
-      const v4u y = *(const v4u*)(src + slot);
-      mac(s0[j], y, *(const v4u*)(kbuf + slot));
-      mac(s1[j], y, *(const v4u*)(kbuf + G::tile + slot));
+      mac(s0[j], y[j], *(const vset*)(lds + kk + at(j)));
+      mac(s1[j], y[j], *(const vset*)(lds + kk + G::tile + at(j)));
     }
     stored_after = jd + 1 == Gr.digits;
     if (stored_after) {
@@ -681,15 +715,27 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
         const uint32_t mm = (uint32_t)v * R.qneg;
         return mul_shoup(reduce_once((uint32_t)(((uint64_t)mm * q + v) >> 32), q), m_r, m_rp, q);
       };
-      const uint32_t ext = Gr.level + set.K;
-      uint32_t* o0 = Gr.acc + ((uint64_t)p.t * Gr.batch + p.b) * N;
-      uint32_t* o1 = Gr.acc + ((uint64_t)(ext + p.t) * Gr.batch + p.b) * N;
+      // into natural order through the key blocks, or through this source's
+      // buffer and the stage: whole-line stores
+      uint32_t* const t0 = kKeep ? src : lds + kKeys;
+      uint32_t* const t1 = lds + (kKeep ? 2 * G::tile : kKeys + G::tile);
+      lds_barrier();  // every wave is done with the keys, or with the source
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const v4u r0 = {fin(s0[j][0]), fin(s0[j][1]), fin(s0[j][2]), fin(s0[j][3])};
-        const v4u r1 = {fin(s1[j][0]), fin(s1[j][1]), fin(s1[j][2]), fin(s1[j][3])};
-        __builtin_nontemporal_store(r0, (v4u*)(o0 + st[j]));
-        __builtin_nontemporal_store(r1, (v4u*)(o1 + st[j]));
+        vset r0, r1;
+#pragma unroll
+        for (int e = 0; e < kSets; ++e) r0[e] = fin(s0[j][e]), r1[e] = fin(s1[j][e]);
+        *(vset*)(t0 + at(j)) = r0;
+        *(vset*)(t1 + at(j)) = r1;
+      }
+      lds_barrier();
+      unsigned char* o0 = (unsigned char*)(Gr.acc + ((uint64_t)(p.t * Gr.batch + p.b) << log_n) + p.blk * G::W);
+      unsigned char* o1 = o0 + (((uint64_t)((Gr.level + set.K) * Gr.batch) << log_n) << 2);
+#pragma unroll
+      for (int j = 0; j < kSets; ++j) {
+        const int slot = (kSets * wave + j) * G::pitch + lane * 4;
+        __builtin_nontemporal_store(*(const v4u*)(t0 + slot), (v4u*)(o0 + st[j]));
+        __builtin_nontemporal_store(*(const v4u*)(t1 + slot), (v4u*)(o1 + st[j]));
       }
     }
     if (!next) break;
@@ -1004,12 +1050,14 @@ hipError_t fs_run_units(const NttUnit* units, uint32_t count, void* ws, hipStrea
   return hipGetLastError();
 }
 
-template <bool kWide>
+template <bool kWide, bool kKeep>
 static hipError_t ip_launch(const tfhe_ntt_plan_s* p, IpSet& set, hipStream_t s) {
   using G = Geo<false, 16, kWide>;
-  const uint32_t ipp = p->n / G::item;  // second-pass items per polynomial (a power of two)
+  constexpr int threads = 2 * G::threads;
+  // second-pass items (resident keys: pairs of items) per polynomial, a power of two
+  const uint32_t ipp = p->n / G::item / (kKeep ? 2 : 1);
   static std::atomic<int> occ{0};
-  const int resident = occupancy_cached(occ, ip_pass<kWide>, G::threads);
+  const int resident = occupancy_cached(occ, ip_pass<kWide, kKeep>, threads);
   uint64_t items = 0;
   for (uint32_t g = 0; g < set.count; ++g) {
     set.g[g].item0 = (uint32_t)items;
@@ -1018,20 +1066,43 @@ static hipError_t ip_launch(const tfhe_ntt_plan_s* p, IpSet& set, hipStream_t s)
   }
   if (items == 0) return hipSuccess;
   if (items >= (1ull << 31)) return hipErrorInvalidValue;  // (more than any memory holds)
-  const uint32_t grid = (uint32_t)std::min<uint64_t>(items, (uint64_t)p->num_cus * resident);
+  uint32_t grid = (uint32_t)std::min<uint64_t>(items, (uint64_t)p->num_cus * resident), share = 0, extra = 0;
+  if (kKeep) {
+    grid = std::max(16u, p->num_cus * resident / 16 * 16);
+    share = (uint32_t)items / (grid / 2);
+    extra = (uint32_t)items % (grid / 2);
+  }
   TFHE_TIMED(K_IP, s,
-             hipLaunchKernelGGL(ip_pass<kWide>, dim3(grid), dim3(G::threads), 0, s, set, p->d_fs_fwd, p->d_mod,
-                                p->log_n, (uint32_t)__builtin_ctz(ipp), div_inv(set.alpha), (uint32_t)items));
+             hipLaunchKernelGGL((ip_pass<kWide, kKeep>), dim3(grid), dim3(threads), 0, s, set, p->d_fs_fwd, p->d_mod,
+                                (const unsigned char*)p->d_fs_blob + sizeof(PassTables), 2 * p->fs_limb_bytes,
+                                p->log_n, (uint32_t)__builtin_ctz(ipp), div_inv(set.alpha), (uint32_t)items, share,
+                                extra));
   return hipGetLastError();
 }
 
 hipError_t ip_run(const tfhe_ntt_plan_s* p, IpSet& set, hipStream_t s) {
   if (set.count == 0) return hipSuccess;
   if (!p->has_mfma) return hipErrorInvalidValue;
-  // wide items need 32 columns of the 256-point stage (N >= 2^13); a plan
-  // that asks for narrow items (fs_wide 1) keeps them here too
-  if (p->fs_wide != 1 && (p->n >> 8) >= 32) return ip_launch<true>(p, set, s);
-  return ip_launch<false>(p, set, s);
+  uint64_t rows = 0, polys = 0;  // extended-basis positions; with their elements
+  uint32_t digits = 0;
+  for (uint32_t g = 0; g < set.count; ++g) {
+    rows += set.g[g].level + set.K;
+    polys += (uint64_t)(set.g[g].level + set.K) * set.g[g].batch;
+    digits = std::max(digits, set.g[g].digits);
+  }
+  const uint64_t narrow = polys * (p->n / Geo<false, 16, false>::item);
+  // Resident keys pay from four elements per key block on, with four narrow
+  // items per workgroup or more (streamed : resident, us, N = 2^16, level 24: two
+  // elements 37 : 39, four 77 : 68, eight 155 : 119; N = 2^14, level 12: eight
+  // 22.6 : 21.0, 64 137 : 124; N = 2^13, level 6: 32 19.5 : 21.5).
+  if (set.keys.count == 1 && digits <= (uint32_t)kKeepDigits && p->n >= (1u << 13) && polys >= 4 * rows &&
+      narrow >= 4ull * p->num_cus)
+    return ip_launch<false, true>(p, set, s);
+  // wide items need 32 columns of the 256-point stage (N >= 2^13), and fewer
+  // narrow ones than CUs run side by side (N = 2^13, level 6: 8.5 us, wide 11.2);
+  // a plan that asks for narrow items (fs_wide 1) keeps them here too
+  if (p->fs_wide != 1 && (p->n >> 8) >= 32 && narrow > p->num_cus) return ip_launch<true, false>(p, set, s);
+  return ip_launch<false, false>(p, set, s);
 }
 
 hipError_t co_transform(const tfhe_ntt_plan_s* p, bool inverse, const uint32_t* in, uint32_t* out,

@@ -242,8 +242,12 @@ static void build_fourstep_limb(FsHostLimb& L, uint32_t log_n, uint32_t q, uint3
         T[a][b] = pow_mod(root, (uint64_t)a * b, q);
         WB[a][b] = pow_mod(root, 16ull * a * b, q);
       }
-    build_pass(pt, 16, WA, T, WB, q, scale, nullptr);
     if (r == 16) co_pass(&pt == &L.p1 ? L.c1 : L.c2, WA, T, WB, q);
+    // the scale goes into the twist, so that opB equals opA (the 16-point DFT
+    // matrix is symmetric) and kernels can keep one of them
+    for (int a = 0; a < 16; ++a)
+      for (int b = 0; b < 16; ++b) T[a][b] = mulm(T[a][b], scale, q);
+    build_pass(pt, 16, WA, T, WB, q, 1, nullptr);
   };
   // natural-order post-twist table of the vector-ALU variant
   auto co_post = [&](auto P) {
@@ -271,17 +275,7 @@ static void build_fourstep_limb(FsHostLimb& L, uint32_t log_n, uint32_t q, uint3
     auto P = [&](int n2, int k1) { return pow_mod(psi, (uint64_t)(2 * k1 + 1) * n2 % twoN, q); };
     build_post(L.post.data(), r, 256, q, r == 16 ? r32 : 1, P);
     if (r == 16) co_post(P);
-    if (r < 16) {
-      // one-pass second pass: the 256-point stage with unscaled level-B
-      // twiddles and the twist carrying 2^64
-      for (int a = 0; a < 16; ++a)
-        for (int b = 0; b < 16; ++b) {
-          WA[a][b] = pow_mod(om, 16ull * a * b, q);
-          T[a][b] = mulm(pow_mod(om, (uint64_t)a * b, q), r32, q);
-          WB[a][b] = WA[a][b];
-        }
-      build_pass(L.op.p2, 16, WA, T, WB, q, 1, nullptr);
-    }
+    L.op.p2 = L.p2;
     build_onepass_post(L.op, r, 256, q, r == 16 ? r32 : 1, P);
   } else {
     cyc256(L.p1, omi, 1);
