@@ -69,11 +69,13 @@ __device__ __forceinline__ v4i mfma(v4i a, v4i b, v4i c) {
 // and carries (see fuse_redc).
 struct Red {
   uint32_t q, qneg, nq, cq, k16;
+  int qs;  // q, its sign unknown to the compiler (else no signed multiply-add)
 };
 __device__ __forceinline__ Red make_red(uint32_t q, uint32_t qneg) {
   uint32_t k16 = 0x10000u;
-  asm("" : "+s"(k16));
-  return Red{q, qneg, 0u - q, 0x80808080u - q, k16};
+  int qs = (int)q;
+  asm("" : "+s"(k16), "+s"(qs));
+  return Red{q, qneg, 0u - q, 0x80808080u - q, k16, qs};
 }
 
 // a b 2^{-32} mod q as (V + m q) / 2^32, V = a b, m = -V q^{-1} mod 2^32:
@@ -94,6 +96,28 @@ __device__ __forceinline__ uint32_t fuse_redc(int c0, int c1, int c2, int c3, co
   const uint32_t m = (uint32_t)V * R.qneg;
   return (uint32_t)(((uint64_t)m * R.q + V) >> 32);
 }
+
+// The same fusion, signed, with the twist in one Montgomery step: V w 2^{-32}
+// mod q for V = (c0 + 2^8 c1) + 2^16 (c2 + 2^8 c3) and t = {w, 2^16 w mod q},
+// below 0.63 q in magnitude.  The halves are below 2^28 + 2^20, so both products
+// with w, w16 < q < 2^31 are below 2^59.1; with m = -T q^{-1} mod 2^32 as a
+// signed number, (T + m q) / 2^32 lies within q (1/8 + 2^-11 + 1/2): inside the
+// digit window as it is (six instructions; fusing, reducing and multiplying one
+// after the other take nine).
+__device__ __forceinline__ int fuse_twist(int c0, int c1, int c2, int c3, uint2 t, const Red& R) {
+  const int lo = (int)((uint32_t)c0 + ((uint32_t)c1 << 8)), hi = (int)((uint32_t)c2 + ((uint32_t)c3 << 8));
+  const int64_t T = (int64_t)hi * (int)t.y + (int64_t)lo * (int)t.x;
+  const int m = (int)((uint32_t)T * R.qneg);
+  return (int)(((int64_t)m * R.qs + T) >> 32);
+}
+// a b 2^{-32} mod q, signed: below |a| |b| 2^{-32} + q / 2 in magnitude.
+__device__ __forceinline__ int mont_signed(int a, int b, const Red& R) {
+  const int64_t T = (int64_t)a * b;
+  const int m = (int)((uint32_t)T * R.qneg);
+  return (int)(((int64_t)m * R.qs + T) >> 32);
+}
+// The residue of v in (-q, q).
+__device__ __forceinline__ uint32_t wrap_signed(int v, uint32_t q) { return min((uint32_t)v, (uint32_t)v + q); }
 
 // Twist (Shoup, t = {w, companion}) and re-slice into digits.  With
 // h = floor(r w' / 2^32) the product z = r w - h q lies in

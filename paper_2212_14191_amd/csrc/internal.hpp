@@ -24,7 +24,7 @@ tfhe_status hip_check(hipError_t e, const char* what);
 // butterflies otherwise).  Laid out exactly as the kernels load them.
 //   opA[j][lane][4]   level-A twiddle operand, digit plane j (4 dwords/lane)
 //   opB[j][lane][4]   level-B twiddle operand (r = 16 only)
-//   twist[lane][j]    twist after level A, {T 2^32 mod q, companion}
+//   twist[lane][j]    twist after level A, {w, 2^16 w mod q} for w = T 2^32 mod q
 //   lb[16]            level-B constants (r < 16): lb[0..3] = rho^0..rho^3 of
 //                     the radix-r root rho; lb[8 + t] = factor of output t
 struct PassTables {
@@ -54,8 +54,8 @@ struct CoPass {
 //            matrix is symmetric).  Inverse (N1-point): opA with the level-A
 //            index u = g + 4c for lane (i, g), dword c, instead of 4g + c.
 //   post_b   [set][j / 2][lane][j % 2] first-pass post-twist, the factor fixed
-//            per lane: P(4m + set, out) (times 2^32 after a matrix-core level
-//            B), Shoup; a lane's 16 bytes lie next to the next lane's, so that
+//            per lane: P(4m + set, out), Shoup; after a matrix-core level B
+//            {w, 2^16 w mod q} for w = 2^32 P; a lane's 16 bytes lie next to the next lane's, so that
 //            LDS copies are read without bank conflicts
 //   post_a   [step][lane][j] the factor of a step whose first column quad is
 //            Q0 = step * 16 / r: P(4 Q0 + 4m, out) / P(4m, out), times 2^32

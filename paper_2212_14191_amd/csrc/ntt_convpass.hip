@@ -261,7 +261,6 @@ cv_pass(const CvTable tab) {
         tw[2 * h] = make_uint2(w[0], w[1]);
         tw[2 * h + 1] = make_uint2(w[2], w[3]);
       }
-      const v4i bias = {(int)q, (int)q, (int)q, (int)q};
       const v4i zero = {0, 0, 0, 0};
 #pragma unroll
       for (int sg = 0; sg < 4; ++sg) {
@@ -281,38 +280,40 @@ cv_pass(const CvTable tab) {
             x[c] = (int)residue_digits_big(y[0][4 * c + sg], q);
           }
         }
-        const v4i a0 = mfma(x, opA[0], bias);
+        const v4i a0 = mfma(x, opA[0], zero);
         const v4i a1 = mfma(x, opA[1], zero);
-        const v4i a2 = mfma(x, opA[2], bias);
+        const v4i a2 = mfma(x, opA[2], zero);
         const v4i a3 = mfma(x, opA[3], zero);
-        uint32_t z[4];
+        // post-twist: the lane's factor (after a matrix-core level B in its
+        // fusion, else Shoup) and the step's (Montgomery)
+        const v4u pbv[2] = {*(const v4u*)(T + S::pb + ((sg * 2) * 64 + lane) * 4),
+                            *(const v4u*)(T + S::pb + ((sg * 2 + 1) * 64 + lane) * 4)};
+        auto pb = [&](int j) { return make_uint2(pbv[j / 2][2 * (j % 2)], pbv[j / 2][2 * (j % 2) + 1]); };
+        uint32_t d[4];
         if (kR == 16) {
           v4i zd;
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            zd[j] = (int)twist_digits(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw[j], R);
-          const v4i b0 = mfma(opB[0], zd, bias);
+          for (int j = 0; j < 4; ++j) zd[j] = (int)residue_digits(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw[j], R));
+          const v4i b0 = mfma(opB[0], zd, zero);
           const v4i b1 = mfma(opB[1], zd, zero);
-          const v4i b2 = mfma(opB[2], zd, bias);
+          const v4i b2 = mfma(opB[2], zd, zero);
           const v4i b3 = mfma(opB[3], zd, zero);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) z[j] = fuse_redc(b0[j], b1[j], b2[j], b3[j], R);
-        } else {
-#pragma unroll
           for (int j = 0; j < 4; ++j)
-            z[j] = reduce_once(mul_shoup_lazy(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw[j].x, tw[j].y, q), q);
+            d[j] = residue_digits(mont_signed(fuse_twist(b0[j], b1[j], b2[j], b3[j], pb(j), R), (int)pa[j], R));
+        } else {
+          uint32_t z[4];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) z[j] = wrap_signed(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw[j], R), q);
           level_b<kR>(z, lb, rj, g, q);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) d[j] = twist_digits(mont_mul_lazy(z[j], pa[j], R), pb(j), R);
         }
-        // post-twist: the step's factor (Montgomery), then the lane's (Shoup)
-        const v4u pbv[2] = {*(const v4u*)(T + S::pb + ((sg * 2) * 64 + lane) * 4),
-                            *(const v4u*)(T + S::pb + ((sg * 2 + 1) * 64 + lane) * 4)};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const uint2 pb = make_uint2(pbv[j / 2][2 * (j % 2)], pbv[j / 2][2 * (j % 2) + 1]);
           int m, t;
           lane_out<kR>(g, j, m, t);
-          gather[t * (1024 / kR) + m * 64 + 16 * (sg ^ g) + i16] =
-              twist_digits(mont_mul_lazy(z[j], pa[j], R), pb, R);
+          gather[t * (1024 / kR) + m * 64 + 16 * (sg ^ g) + i16] = d[j];
         }
       }
     };

@@ -271,26 +271,28 @@ fs_pass(const FsTable tab) {
         }
         const v4i bias = {(int)q, (int)q, (int)q, (int)q};
         const v4i zero = {0, 0, 0, 0};
-        const v4i a0 = mfma(x, opA[0], bias);
+        const v4i a0 = mfma(x, opA[0], zero);
         const v4i a1 = mfma(x, opA[1], zero);
-        const v4i a2 = mfma(x, opA[2], bias);
+        const v4i a2 = mfma(x, opA[2], zero);
         const v4i a3 = mfma(x, opA[3], zero);
         uint32_t y[4];
         if (kR == 16) {
           v4i z;
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            z[j] = (int)twist_digits(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw[j], R);
-          const v4i b0 = mfma(opB[0], z, bias);
+            z[j] = (int)residue_digits(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw[j], R));
+          const v4i b0 = mfma(opB[0], z, kFirst ? zero : bias);
           const v4i b1 = mfma(opB[1], z, zero);
-          const v4i b2 = mfma(opB[2], z, bias);
+          const v4i b2 = mfma(opB[2], z, kFirst ? zero : bias);
           const v4i b3 = mfma(opB[3], z, zero);
 #pragma unroll
-          for (int j = 0; j < 4; ++j) y[j] = fuse_redc(b0[j], b1[j], b2[j], b3[j], R);
+          for (int j = 0; j < 4; ++j)
+            y[j] = kFirst ? residue_digits(fuse_twist(b0[j], b1[j], b2[j], b3[j], pt[sg][j], R))
+                          : fuse_redc(b0[j], b1[j], b2[j], b3[j], R);
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            y[j] = reduce_once(mul_shoup_lazy(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw[j].x, tw[j].y, q), q);
+            y[j] = wrap_signed(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw[j], R), q);
           level_b<kR>(y, lb, rj, g, q);
         }
         if (kGather) {
@@ -299,10 +301,10 @@ fs_pass(const FsTable tab) {
           // four lane groups write disjoint banks
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            gather[(4 * g + j) * 64 + 16 * (sg ^ g) + i16] = twist_digits(y[j], pt[sg][j], R);
+            gather[(4 * g + j) * 64 + 16 * (sg ^ g) + i16] = y[j];
         } else if (kFirst) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) out[st_off[j] + 16 * sg] = twist_digits(y[j], pt[sg][j], R);
+          for (int j = 0; j < 4; ++j) out[st_off[j] + 16 * sg] = kR == 16 ? y[j] : twist_digits(y[j], pt[sg][j], R);
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
@@ -666,14 +668,14 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
 #pragma unroll
       for (int sg = 0; sg < kSets; ++sg) {
         const v4i x = {(int)rows[0][sg], (int)rows[1][sg], (int)rows[2][sg], (int)rows[3][sg]};
-        const v4i a0 = mfma(x, opA[0], bias);
+        const v4i a0 = mfma(x, opA[0], zero);
         const v4i a1 = mfma(x, opA[1], zero);
-        const v4i a2 = mfma(x, opA[2], bias);
+        const v4i a2 = mfma(x, opA[2], zero);
         const v4i a3 = mfma(x, opA[3], zero);
         v4i z;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          z[j] = (int)twist_digits(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw[j], R);
+          z[j] = (int)residue_digits(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw[j], R));
         // level B: the same symmetric matrix (the twist carries its 2^32)
         const v4i b0 = mfma(opA[0], z, bias);
         const v4i b1 = mfma(opA[1], z, zero);

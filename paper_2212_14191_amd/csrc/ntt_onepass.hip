@@ -234,7 +234,8 @@ op_kernel(const FsTable tab) {
         const int ai = opaque(i16), ag = opaque(g);  // for addresses
         if (st > 0) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) pa[j] = mont_mul_lazy(pa[j], pad[j], R);
+          for (int j = 0; j < 4; ++j)
+            pa[j] = kR1 == 16 ? (uint32_t)mont_signed((int)pa[j], (int)pad[j], R) : mont_mul_lazy(pa[j], pad[j], R);
         }
         uint4 rows[4];
 #pragma unroll
@@ -256,34 +257,34 @@ op_kernel(const FsTable tab) {
             const uint32_t w = sg == 0 ? rows[c].x : sg == 1 ? rows[c].y : sg == 2 ? rows[c].z : rows[c].w;
             x[c] = (int)(kBigQ ? residue_digits_big(w, q) : residue_digits(w));
           }
-          const v4i a0 = mfma(x, opA1[0], bias);
+          const v4i a0 = mfma(x, opA1[0], zero);
           const v4i a1 = mfma(x, opA1[1], zero);
-          const v4i a2 = mfma(x, opA1[2], bias);
+          const v4i a2 = mfma(x, opA1[2], zero);
           const v4i a3 = mfma(x, opA1[3], zero);
           uint32_t y[4];
           if (kR1 == 16) {
             v4i z;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              z[j] = (int)twist_digits(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw1[j], R);
+              z[j] = (int)residue_digits(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw1[j], R));
             // level B (only the inverse's 256-point stage here): the same
             // symmetric matrix, unscaled, so opB equals opA
-            const v4i b0 = mfma(opA1[0], z, bias);
+            const v4i b0 = mfma(opA1[0], z, zero);
             const v4i b1 = mfma(opA1[1], z, zero);
-            const v4i b2 = mfma(opA1[2], z, bias);
+            const v4i b2 = mfma(opA1[2], z, zero);
             const v4i b3 = mfma(opA1[3], z, zero);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) y[j] = fuse_redc(b0[j], b1[j], b2[j], b3[j], R);
+            for (int j = 0; j < 4; ++j)
+              y[j] = (uint32_t)mont_signed(fuse_twist(b0[j], b1[j], b2[j], b3[j], pb[j][sg], R), (int)pa[j], R);
           } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              y[j] = reduce_once(mul_shoup_lazy(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw1[j].x,
-                                                tw1[j].y, q), q);
+              y[j] = wrap_signed(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw1[j], R), q);
             level_b<kR1>(y, lb1, rj, g, q);
           }
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            o[j][sg] = twist_digits(mont_mul_lazy(y[j], pa[j], R), pb[j][sg], R);
+            o[j][sg] = kR1 == 16 ? residue_digits(y[j]) : twist_digits(mont_mul_lazy(y[j], pa[j], R), pb[j][sg], R);
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -334,16 +335,16 @@ op_kernel(const FsTable tab) {
             const int row = R0 + 4 * (ai / kR2) + sg, e = kR2 * u + ai % kR2;
             x[c] = (int)buf[sw_in<C::in_a, C::in_b>(row * S + e)];
           }
-          const v4i a0 = mfma(x, opA2[0], bias);
+          const v4i a0 = mfma(x, opA2[0], zero);
           const v4i a1 = mfma(x, opA2[1], zero);
-          const v4i a2 = mfma(x, opA2[2], bias);
+          const v4i a2 = mfma(x, opA2[2], zero);
           const v4i a3 = mfma(x, opA2[3], zero);
           uint32_t y[4];
           if (kR2 == 16) {
             v4i z;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              z[j] = (int)twist_digits(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw2[j], R);
+              z[j] = (int)residue_digits(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw2[j], R));
             const v4i b0 = mfma(opA2[0], z, bias);  // level B: the same symmetric matrix
             const v4i b1 = mfma(opA2[1], z, zero);
             const v4i b2 = mfma(opA2[2], z, bias);
@@ -353,8 +354,7 @@ op_kernel(const FsTable tab) {
           } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              y[j] = reduce_once(mul_shoup_lazy(fuse_redc(a0[j], a1[j], a2[j], a3[j], R), tw2[j].x,
-                                                tw2[j].y, q), q);
+              y[j] = wrap_signed(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw2[j], R), q);
             level_b<kR2>(y, lb2, rj, g, q);
 #pragma unroll
             for (int j = 0; j < 4; ++j) y[j] = mul_shoup(y[j], pf[j].x, pf[j].y, q);

@@ -150,7 +150,7 @@ static void build_pass(PassTables& pt, int r, const Mat16& WA, const Mat16& T, c
     for (int j = 0; j < 4; ++j) {
       const int v = (4 * (lane / 16) + j) % r;
       uint32_t w = mulm(T[lane % 16][v], tw_scale, q);
-      pt.twist[lane][j] = make_uint2(w, shoup_companion(w, q));
+      pt.twist[lane][j] = make_uint2(w, mulm(w, 1u << 16, q));
     }
   for (int i = 0; i < 16; ++i) {
     uint32_t w = lb ? lb[i] % q : 0;
@@ -171,7 +171,7 @@ static void build_post(uint2* post, int r, int ncols, uint32_t q, uint32_t scale
         lane_output(r, lane, j, &m, &t);
         const int col = b + 4 * m, k = lane % 16 + 16 * t;
         uint32_t w = col < ncols ? mulm(P(col, k), scale, q) : 0;
-        post[(b * 64 + lane) * 4 + j] = make_uint2(w, shoup_companion(w, q));
+        post[(b * 64 + lane) * 4 + j] = make_uint2(w, r == 16 ? mulm(w, 1u << 16, q) : shoup_companion(w, q));
       }
 }
 
@@ -189,7 +189,7 @@ static void build_onepass_post(OnePassTables& op, int r1, int ncols, uint32_t q,
       const int out = lane % 16 + 16 * t;
       for (int sg = 0; sg < 4; ++sg) {
         const uint32_t w = mulm(P(4 * m + sg, out), scale, q);
-        op.post_b[sg][j / 2][lane][j % 2] = make_uint2(w, shoup_companion(w, q));
+        op.post_b[sg][j / 2][lane][j % 2] = make_uint2(w, r1 == 16 ? mulm(w, 1u << 16, q) : shoup_companion(w, q));
       }
       // geometric in the step: P(4 st mt + 4 m, out) / P(4 m, out)
       const uint32_t ratio = mulm(P(4 * mt % ncols, out), inv_mod(P(0, out), q), q);
@@ -321,7 +321,7 @@ void scaled_twist(const tfhe_ntt_plan_s* p, uint32_t limb, uint32_t scale, std::
       const uint32_t s = lane % 16, v = (4 * (lane / 16) + j) % r;
       // r = 16: T[s][v] = phi^{-(2v+1)s}; r < 16: phi^{-(2v+1)s} as well, [s][v]
       const uint32_t w = mulm(pow_mod(phii, (uint64_t)(2 * v + 1) * s, q), f, q);
-      out.push_back(make_uint2(w, shoup_companion(w, q)));
+      out.push_back(make_uint2(w, mulm(w, 1u << 16, q)));
     }
 }
 
