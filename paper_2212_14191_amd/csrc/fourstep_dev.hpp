@@ -78,6 +78,14 @@ __device__ __forceinline__ Red make_red(uint32_t q, uint32_t qneg) {
   return Red{q, qneg, 0u - q, 0x80808080u - q, k16, qs};
 }
 
+// The modulus for a block of code that multiplies by qs: its sign extension,
+// kept from another block, would make a 64 x 64 bit product of every one.
+__device__ __forceinline__ Red local(const Red& R) {
+  Red r = R;
+  asm volatile("" : "+s"(r.qs));
+  return r;
+}
+
 // a b 2^{-32} mod q as (V + m q) / 2^32, V = a b, m = -V q^{-1} mod 2^32:
 // below 2^32 for any a, b < 2^32, and below 2q for a, b < q (not reduced).
 __device__ __forceinline__ uint32_t mont_mul_lazy(uint32_t a, uint32_t b, const Red& R) {

@@ -247,6 +247,7 @@ fs_pass(const FsTable tab) {
     uint32_t* const out = tab.u[it.unit].out + it.poly_base;
     uint4 res[4];  // pass 2: res[j] = the four sets' outputs of register j
     const uint32_t q = R.q;
+    const Red M = local(R);
     if (kFirst) {
       // only moduli above 0x7F7F7F7F (uniform) need the window's correction
       if (q > 0x7F7F7F7Fu) {
@@ -280,19 +281,19 @@ fs_pass(const FsTable tab) {
           v4i z;
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            z[j] = (int)residue_digits(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw[j], R));
+            z[j] = (int)residue_digits(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw[j], M));
           const v4i b0 = mfma(opB[0], z, kFirst ? zero : bias);
           const v4i b1 = mfma(opB[1], z, zero);
           const v4i b2 = mfma(opB[2], z, kFirst ? zero : bias);
           const v4i b3 = mfma(opB[3], z, zero);
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            y[j] = kFirst ? residue_digits(fuse_twist(b0[j], b1[j], b2[j], b3[j], pt[sg][j], R))
-                          : fuse_redc(b0[j], b1[j], b2[j], b3[j], R);
+            y[j] = kFirst ? residue_digits(fuse_twist(b0[j], b1[j], b2[j], b3[j], pt[sg][j], M))
+                          : fuse_redc(b0[j], b1[j], b2[j], b3[j], M);
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            y[j] = wrap_signed(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw[j], R), q);
+            y[j] = wrap_signed(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw[j], M), q);
           level_b<kR>(y, lb, rj, g, q);
         }
         if (kGather) {
@@ -304,7 +305,7 @@ fs_pass(const FsTable tab) {
             gather[(4 * g + j) * 64 + 16 * (sg ^ g) + i16] = y[j];
         } else if (kFirst) {
 #pragma unroll
-          for (int j = 0; j < 4; ++j) out[st_off[j] + 16 * sg] = kR == 16 ? y[j] : twist_digits(y[j], pt[sg][j], R);
+          for (int j = 0; j < 4; ++j) out[st_off[j] + 16 * sg] = kR == 16 ? y[j] : twist_digits(y[j], pt[sg][j], M);
         } else {
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
@@ -657,6 +658,7 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
     };
     vset y[4];
     if (jd != p.own) {
+      const Red M = local(R);
       vset rows[4];
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
@@ -675,14 +677,14 @@ ip_pass(const IpSet set, const FourStepLimb* __restrict__ limbs, const ModConst*
         v4i z;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          z[j] = (int)residue_digits(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw[j], R));
+          z[j] = (int)residue_digits(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw[j], M));
         // level B: the same symmetric matrix (the twist carries its 2^32)
         const v4i b0 = mfma(opA[0], z, bias);
         const v4i b1 = mfma(opA[1], z, zero);
         const v4i b2 = mfma(opA[2], z, bias);
         const v4i b3 = mfma(opA[3], z, zero);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) y[j][sg] = fuse_redc(b0[j], b1[j], b2[j], b3[j], R);
+        for (int j = 0; j < 4; ++j) y[j][sg] = fuse_redc(b0[j], b1[j], b2[j], b3[j], M);
       }
     } else {
 #pragma unroll

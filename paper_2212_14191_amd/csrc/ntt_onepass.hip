@@ -214,8 +214,7 @@ op_kernel(const FsTable tab) {
     // ---- pass 1: columns, in place.  Lane (i, g) reads row
     // kR1 (4g + c) + i % kR1 of quad Q0 + i / kR1 (the four sets are the
     // quad's four columns) and writes output s + 16 t of column quad Q0 + m.
-    auto pass1 = [&](auto big_q) {
-      constexpr bool kBigQ = decltype(big_q)::value;
+    {
       v4i opA1[4];
       uint2 tw1[4], pb[4][4];
 #pragma unroll
@@ -243,6 +242,19 @@ op_kernel(const FsTable tab) {
           const int row = kR1 * (4 * ag + c) + ai % kR1, quad = Q0 + ai / kR1;
           rows[c] = *(const uint4*)(buf + sw_in<C::in_a, C::in_b>(row * S + 4 * quad));
         }
+        // only moduli above 0x7F7F7F7F (uniform) need the window's correction
+        if (q > 0x7F7F7F7Fu) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            rows[c] = make_uint4(residue_digits_big(rows[c].x, q), residue_digits_big(rows[c].y, q),
+                                 residue_digits_big(rows[c].z, q), residue_digits_big(rows[c].w, q));
+        } else {
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            rows[c] = make_uint4(residue_digits(rows[c].x), residue_digits(rows[c].y), residue_digits(rows[c].z),
+                                 residue_digits(rows[c].w));
+        }
+        const Red M = local(R);
         uint32_t o[4][4];  // [register j][set]
         uint2 rj[4];
         if (kR1 == 8) {
@@ -254,8 +266,7 @@ op_kernel(const FsTable tab) {
           v4i x;
 #pragma unroll
           for (int c = 0; c < 4; ++c) {
-            const uint32_t w = sg == 0 ? rows[c].x : sg == 1 ? rows[c].y : sg == 2 ? rows[c].z : rows[c].w;
-            x[c] = (int)(kBigQ ? residue_digits_big(w, q) : residue_digits(w));
+            x[c] = (int)(sg == 0 ? rows[c].x : sg == 1 ? rows[c].y : sg == 2 ? rows[c].z : rows[c].w);
           }
           const v4i a0 = mfma(x, opA1[0], zero);
           const v4i a1 = mfma(x, opA1[1], zero);
@@ -266,7 +277,7 @@ op_kernel(const FsTable tab) {
             v4i z;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              z[j] = (int)residue_digits(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw1[j], R));
+              z[j] = (int)residue_digits(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw1[j], M));
             // level B (only the inverse's 256-point stage here): the same
             // symmetric matrix, unscaled, so opB equals opA
             const v4i b0 = mfma(opA1[0], z, zero);
@@ -275,16 +286,16 @@ op_kernel(const FsTable tab) {
             const v4i b3 = mfma(opA1[3], z, zero);
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              y[j] = (uint32_t)mont_signed(fuse_twist(b0[j], b1[j], b2[j], b3[j], pb[j][sg], R), (int)pa[j], R);
+              y[j] = (uint32_t)mont_signed(fuse_twist(b0[j], b1[j], b2[j], b3[j], pb[j][sg], M), (int)pa[j], M);
           } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              y[j] = wrap_signed(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw1[j], R), q);
+              y[j] = wrap_signed(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw1[j], M), q);
             level_b<kR1>(y, lb1, rj, g, q);
           }
 #pragma unroll
           for (int j = 0; j < 4; ++j)
-            o[j][sg] = kR1 == 16 ? residue_digits(y[j]) : twist_digits(mont_mul_lazy(y[j], pa[j], R), pb[j][sg], R);
+            o[j][sg] = kR1 == 16 ? residue_digits(y[j]) : twist_digits(mont_mul_lazy(y[j], pa[j], M), pb[j][sg], M);
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -295,9 +306,7 @@ op_kernel(const FsTable tab) {
               make_uint4(o[j][0], o[j][1], o[j][2], o[j][3]);
         }
       }
-    };
-    if (q > 0x7F7F7F7Fu) pass1(std::true_type{});
-    else pass1(std::false_type{});
+    }
     lds_barrier();
 
     // ---- pass 2: rows.  Step rows R0 .. R0 + 4 Mt2 - 1; set sg and tile
@@ -305,6 +314,7 @@ op_kernel(const FsTable tab) {
     // kR2 u + i % kR2 (u = 4g + c, or g + 4c for the inverse).
     uint4 res[St2][4];
     {
+      const Red M = local(R);
       v4i opA2[4];
       uint2 tw2[4];
 #pragma unroll
@@ -322,19 +332,28 @@ op_kernel(const FsTable tab) {
           rj[j] = (g & 1) ? lb2[j] : lb2[0];
         }
       }
+      // the first step's 16 word addresses; a step further lies kStep words on,
+      // whole chunks that leave the swizzle as it is (computed per step, the
+      // addresses took a quarter of this pass's instructions)
+      constexpr int kStep = W * 4 * Mt2 * S;
+      static_assert(kStep % 256 == 0 && C::in_a * (kStep / 256) % 16 == 0, "step against swizzle");
+      int at[4][4];
+      const int ai = opaque(i16), ag = opaque(g);
+#pragma unroll
+      for (int sg = 0; sg < 4; ++sg)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const int u = kUA ? ag + 4 * c : 4 * ag + c;
+          const int row = wave * 4 * Mt2 + 4 * (ai / kR2) + sg, e = kR2 * u + ai % kR2;
+          at[sg][c] = sw_in<C::in_a, C::in_b>(row * S + e);
+        }
 #pragma unroll
       for (int st = 0; st < St2; ++st) {
-        const int R0 = (wave + st * W) * 4 * Mt2;
 #pragma unroll
         for (int sg = 0; sg < 4; ++sg) {
-          const int ai = opaque(i16), ag = opaque(g);  // for addresses
           v4i x;
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const int u = kUA ? ag + 4 * c : 4 * ag + c;
-            const int row = R0 + 4 * (ai / kR2) + sg, e = kR2 * u + ai % kR2;
-            x[c] = (int)buf[sw_in<C::in_a, C::in_b>(row * S + e)];
-          }
+          for (int c = 0; c < 4; ++c) x[c] = (int)buf[at[sg][c] + st * kStep];
           const v4i a0 = mfma(x, opA2[0], zero);
           const v4i a1 = mfma(x, opA2[1], zero);
           const v4i a2 = mfma(x, opA2[2], zero);
@@ -344,17 +363,17 @@ op_kernel(const FsTable tab) {
             v4i z;
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              z[j] = (int)residue_digits(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw2[j], R));
+              z[j] = (int)residue_digits(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw2[j], M));
             const v4i b0 = mfma(opA2[0], z, bias);  // level B: the same symmetric matrix
             const v4i b1 = mfma(opA2[1], z, zero);
             const v4i b2 = mfma(opA2[2], z, bias);
             const v4i b3 = mfma(opA2[3], z, zero);
 #pragma unroll
-            for (int j = 0; j < 4; ++j) y[j] = reduce_once(fuse_redc(b0[j], b1[j], b2[j], b3[j], R), q);
+            for (int j = 0; j < 4; ++j) y[j] = reduce_once(fuse_redc(b0[j], b1[j], b2[j], b3[j], M), q);
           } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-              y[j] = wrap_signed(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw2[j], R), q);
+              y[j] = wrap_signed(fuse_twist(a0[j], a1[j], a2[j], a3[j], tw2[j], M), q);
             level_b<kR2>(y, lb2, rj, g, q);
 #pragma unroll
             for (int j = 0; j < 4; ++j) y[j] = mul_shoup(y[j], pf[j].x, pf[j].y, q);
