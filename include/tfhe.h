@@ -125,9 +125,9 @@ tfhe_status tfhe_ntt_plan_modulus(tfhe_ntt_plan plan, uint32_t limb, uint32_t* q
  *                            epilogue, which keep two), 2 = two (a
  *                            transposed intermediate in the workspace
  *                            between two passes), 0 = library default: one
- *                            at N = 2^12, and at N = 2^13 and 2^14 (forward
- *                            also 2^15) where the launch's polynomials fill
- *                            the compute units, else two.  Same results.
+ *                            at N = 2^12 and 2^13, and at N = 2^14 and 2^15
+ *                            where the launch's polynomials fill the compute
+ *                            units, else two.  Same results.
  *   TFHE_PARAM_KS_INNER      key switching with a four-step plan (the plan
  *                            of a CKKS context): 0 = library default (1),
  *                            1 = the ModUp transforms' second pass fused

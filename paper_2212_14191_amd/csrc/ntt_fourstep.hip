@@ -928,26 +928,25 @@ size_t fs_workspace_bytes(const tfhe_ntt_plan_s* p, uint32_t limb_count, uint32_
 
 // Whether a launch of `polys` four-step transforms of this plan takes the
 // one-pass kernel: always with fs_passes 1, never with 2.  By default where it
-// measured faster than two passes (us, one pass : two passes, forward, C = 256
-// CUs; the inverse lies within 5 % of it):
-//   2^12  always: 5.6 : 6.9 (8 polynomials), 8.5 : 10.3 (512);
-//   2^13  7.7 : 7.7 (64), 8.0 : 8.4 (128), 8.7 : 10.9 (256), 13.4 : 12.8 (320),
-//         13.5 : 13.7 (384), 14.5 : 23.5 (508);
-//   2^14  13.9 : 12.9 (128), 13.8 : 14.8 (144), 15.9 : 25.1 (256), 24.1 : 24.9
-//         (264), 25.8 : 37.6 (508);
-//   2^15  forward 29.2 : 26.7 (128), 28.7 : 31.5 (144), 31.9 : 40.8 (256), 55.8 :
-//         42.2 (264), 62.8 : 66.2 (508); inverse 36.4 : 36.2 (256), else slower.
-// A workgroup holds one whole polynomial, so few polynomials leave CUs idle,
-// and a little more than one (2^15: any more) per CU means a second round.
+// measured faster than two passes (us, one pass : two passes, forward / inverse,
+// C = 256 CUs):
+//   2^12  always: 4.8 : 6.7 (8 polynomials), 7.0 : 9.9 (508), 19.8 : 33.8 (2048);
+//   2^13  always: 6.5 / 6.9 : 7.2 / 7.0 (8), 7.2 : 8.1 (128), 11.7 : 13.4 (384);
+//   2^14  11.4 : 8.9 (64), 12.1 / 12.2 : 12.8 / 12.1 (128), 13.7 : 24.7 (256),
+//         21.2 : 26.6 (384), 81 : 111 (2048);
+//   2^15  25.2 / 27.7 : 26.0 / 23.6 (128), 28.2 / 32.3 : 40.5 / 36.8 (256),
+//         51.7 / 56.4 : 52.7 / 50.1 (384), 214 / 221 : 208 / 228 (2048).
+// A workgroup holds one whole polynomial: few polynomials leave CUs idle, and at
+// 2^15 one is alone on its CU, so more than one per CU means a second round.
 static bool use_onepass(const tfhe_ntt_plan_s* p, bool inverse, uint64_t polys) {
   if (!op_supported(p->log_n) || p->fs_passes == 2) return false;
   if (p->fs_passes == 1) return true;
   const uint64_t C = p->num_cus;
   switch (p->log_n) {
-    case 12: return true;
-    case 13: return 2 * polys >= C && (polys <= C || 2 * polys >= 3 * C);
-    case 14: return 2 * polys > C;
-    default: return !inverse && 2 * polys > C && polys <= C;
+    case 12:
+    case 13: return true;
+    case 14: return 2 * polys >= C;
+    default: return 4 * polys >= (inverse ? 3 : 2) * C && polys <= C;
   }
 }
 

@@ -15,8 +15,8 @@
 // the others' arithmetic (measured faster than one 8-wave workgroup that
 // double-buffers: 1.2-1.25 x at 2^13 and 2^14).  A launch of no more
 // polynomials than CUs has nothing to overlap and takes 8 waves at 2^13 and
-// 2^14 (256 polynomials: 9.7 -> 8.7 and 17.4 -> 15.8 us; 16 waves at 2^14
-// have too few registers: 24.8).  At 2^15 the polynomial takes 128 KiB and one
+// 2^14 (256 polynomials: 9.7 -> 8.7 and 17.4 -> 15.8 us when introduced, 7.7
+// and 13.7 now; 16 waves at 2^14 had too few registers: 24.8).  At 2^15 the polynomial takes 128 KiB and one
 // workgroup of 8 waves owns the CU.
 //
 // LDS layout: 1 KiB chunks of the polynomial in order; inside a chunk the
@@ -255,6 +255,15 @@ op_kernel(const FsTable tab) {
                                  residue_digits(rows[c].w));
         }
         const Red M = local(R);
+        // (nor the twists' sign extensions from another step)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          asm volatile("" : "+v"(tw1[j].x), "+v"(tw1[j].y));
+          if (kR1 == 16) {
+#pragma unroll
+            for (int sg = 0; sg < 4; ++sg) asm volatile("" : "+v"(pb[j][sg].x), "+v"(pb[j][sg].y));
+          }
+        }
         uint32_t o[4][4];  // [register j][set]
         uint2 rj[4];
         if (kR1 == 8) {
