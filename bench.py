@@ -47,7 +47,7 @@ TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "ntt_mfma_n16_44x128.md")
 # the HMULT benchmark's kernels: the transforms plus the key-switching code,
 # and the rules that set its context's launch shape
 HMULT_SOURCES = TRAFFIC_SOURCES + ("csrc/ckks.cpp", "csrc/ckks_kernels.hip", "csrc/ckks_internal.hpp",
-                                   "autotune.py")
+                                   "csrc/ntt_convpass.hip", "autotune.py")
 HMULT_PROFILE = os.path.join(ROOT, "profiles", "hmult_n16_l24_b64.md")
 
 
@@ -605,7 +605,7 @@ def main():
         tfhe.tfhe_timing_enable(True)
         dt = timed(hstep, args.hmult_steps, sync)
         kern = {}
-        for name in ("ntt_mfma_pass1", "ntt_mfma_pass2", "ntt_mfma_pass2_inner", "ckks_tensor", "ckks_modup",
+        for name in ("ntt_mfma_pass1", "ntt_mfma_conv_pass1", "ntt_mfma_pass2", "ntt_mfma_pass2_inner", "ckks_tensor", "ckks_modup",
                      "ckks_inner", "ckks_moddown_conv", "ckks_moddown_final"):
             cnt, ms = tfhe.tfhe_timing_read(name)
             kern[name] = {"launches": cnt, "total_ms": ms}
@@ -623,7 +623,7 @@ def main():
         tfhe.tfhe_timing_enable(True)
         dt = timed(rstep, args.hmult_steps, sync)
         rk = {}
-        for name in ("ntt_mfma_pass1", "ntt_mfma_pass2", "ckks_rescale_bcast", "ckks_rescale_final"):
+        for name in ("ntt_mfma_pass1", "ntt_mfma_conv_pass1", "ntt_mfma_pass2", "ckks_rescale_bcast", "ckks_rescale_final"):
             cnt, ms = tfhe.tfhe_timing_read(name)
             rk[name] = {"launches": cnt, "total_ms": ms}
         tfhe.tfhe_timing_enable(False)

@@ -66,15 +66,12 @@ struct OnePassTables {
   uint32_t post_a[64][64][4];
 };
 
-// Device-side description of one limb for the four-step kernels.
+// Device-side description of one limb for the four-step kernels (the matrix-core
+// kernels' tables lie at computed places: tfhe_plan_impl::d_fs_blob).
 struct FourStepLimb {
-  const PassTables* pass1;  // first pass (its post-twist: post1)
-  const PassTables* pass2;  // second pass
-  const uint2* post1;       // [256 column bases][64 lanes][4]: post-twist of pass 1
   const CoPass* co1;        // vector-ALU variant (N = 2^16 only): pass matrices
   const CoPass* co2;
   const uint2* co_post;     // [256 columns][256 outputs]: post-twist of pass 1
-  const OnePassTables* op;  // one-pass kernel (its p2: N = 2^12..2^15)
   uint32_t q, qneg;         // modulus and -q^{-1} mod 2^32
 };
 
@@ -99,7 +96,7 @@ struct tfhe_plan_impl {
   FourStepLimb* d_fs_fwd = nullptr;  // [n_limbs]
   FourStepLimb* d_fs_inv = nullptr;  // [n_limbs]
   void* d_fs_blob = nullptr;          // owns all four-step tables: limb l, direction d at (2 l + d) fs_limb_bytes
-  size_t fs_limb_bytes = 0;           // (pass 1's PassTables at 0, OnePassTables at fs_op_off)
+  size_t fs_limb_bytes = 0;           // (PassTables of pass 1 and 2, pass 1's post-twist, OnePassTables at fs_op_off)
   size_t fs_op_off = 0;
   std::vector<void*> owned;
 };

@@ -391,13 +391,9 @@ tfhe_status plan_build(tfhe_ntt_plan_s* p) {
         memcpy(&blob[off + sizeof(PassTables)], &H.p2, sizeof(PassTables));
         memcpy(&blob[off + 2 * sizeof(PassTables)], H.post.data(), post_elems * sizeof(uint2));
         FourStepLimb& f = dir == 0 ? hf[l] : hi[l];
-        f.pass1 = (const PassTables*)(dbase + off);
-        f.pass2 = (const PassTables*)(dbase + off + sizeof(PassTables));
-        f.post1 = (const uint2*)(dbase + off + 2 * sizeof(PassTables));
         f.co1 = f.co2 = nullptr;
         f.co_post = nullptr;
         memcpy(&blob[off + op_off], &H.op, sizeof(OnePassTables));
-        f.op = (const OnePassTables*)(dbase + off + op_off);
         if (co) {
           const size_t o2 = off + 2 * sizeof(PassTables) + post_elems * sizeof(uint2);
           memcpy(&blob[o2], &H.c1, sizeof(CoPass));
