@@ -482,7 +482,7 @@ void launch_pass_r(const tfhe_ntt_plan_s* p, uint32_t r, const FsTable& t, hipSt
 // arithmetic the streaming kernel takes as long).  64 pairs at N = 2^16, level
 // 24, three digits: 0.98 ms with the products in natural order (each task's
 // results through LDS, three barriers), 0.91 streamed, 0.72 resident, against
-// 0.61 for the HBM bytes at the copy rate.
+// 0.55 for its HBM bytes at the copy rate.
 constexpr int kKeepDigits = 3;
 template <bool kWide, bool kKeep>
 __global__ void __launch_bounds__((2 * Geo<false, 16, kWide>::threads), (kKeep ? 2 : 4))
