@@ -478,7 +478,8 @@ tfhe_status tfhe_timing_enable(int enable);
 
 /* Launch count and summed event-measured duration (ms) of the kernel named
  * `kernel` since timing was enabled; waits for the recorded events.  Names:
- * ntt_mfma_pass1, ntt_mfma_pass2, ntt_mfma_onepass, ntt_mfma_pass2_inner, ntt_co_pass1,
+ * ntt_mfma_pass1, ntt_mfma_conv_pass1, ntt_mfma_pass2, ntt_mfma_onepass,
+ * ntt_mfma_pass2_inner, ntt_co_pass1,
  * ntt_co_pass2, ntt_bf_single,
  * ntt_bf_cols, ntt_bf_rows,
  * elementwise, ckks_tensor, ckks_modup, ckks_inner, ckks_moddown_conv,

@@ -16,15 +16,15 @@
 // between waves: one multiply-add per input and coefficient, then the matrix
 // cores.  What changes per target is the limb's tables (operands, twist,
 // post-twist: 14 or 18 KiB), which the waves of a workgroup read from an LDS
-// copy that is loaded one target ahead.  Bound by the vector ALUs (about 36
+// copy that is loaded one target ahead.  Bound by the vector ALUs (32-37
 // instructions per coefficient and target, two waves per SIMD).
 //
 // Measured for 64 pairs at N = 2^16, level 24, as a kernel of its own that
 // wrote the converted planes and a plain first pass -> here: ModUp 0.31 + 0.49
-// -> 0.53 ms, ModDown 0.20 + 0.34 -> 0.36 ms, RESCALE's first pass 0.34 ->
-// 0.24 ms.  The same conversion on the matrix cores (byte digits of y against
+// -> 0.51 ms, ModDown 0.20 + 0.34 -> 0.34 ms, RESCALE's first pass 0.34 ->
+// 0.21 ms.  The same conversion on the matrix cores (byte digits of y against
 // byte digits of the constants) takes fewer vector instructions but 0.60 ms
-// for ModUp: its operands go through LDS and the matrix cores' cycles are
+// for ModUp (0.53 here then): its operands go through LDS and the matrix cores' cycles are
 // taken from the same SIMD.
 //
 // Exactness: the inputs enter as y_r - 2^30 in [-2^30, 2^30) and the

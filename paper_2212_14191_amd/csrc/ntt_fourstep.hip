@@ -23,12 +23,13 @@
 // bytes, one v_mfma_i32_16x16x64_i8 per twiddle digit plane j yields
 //   C_j = sum_u sum_d x_d[u] * digit_j(W^(d)[u])   (|C_j| <= 2^20, exact)
 // and V = sum_j 2^{8j} C_j = sum_u x[u] w[u] (mod q).  The "fusion" step
-// forms V = (C_0 + 2^8 C_1) + 2^16 (C_2 + 2^8 C_3) (C_0 and C_2 start at q
-// so both halves are positive), reduces it by one Montgomery step to
-// V 2^{-32} mod q, and multiplies by the next twist (stored as t 2^32, Shoup
-// form), or, after a last matrix-core level whose twiddles carry the 2^32,
-// leaves the canonical residue.  Twisted results are re-sliced into digits
-// for the next contraction with two VALU operations.
+// forms V = (C_0 + 2^8 C_1) + 2^16 (C_2 + 2^8 C_3).  Where a twist follows, its
+// two halves are multiplied by t 2^32 and t 2^48 and reduced by one signed
+// Montgomery step (fuse_twist); after a last matrix-core level, whose twiddles or
+// twist carry the 2^32, C_0 and C_2 start at q so that both halves are positive,
+// and one Montgomery step leaves the canonical residue (fuse_redc).  Twisted
+// results are re-sliced into digits for the next contraction with two VALU
+// operations.
 //
 // Data movement.  A work item is P rows x W columns (vectors) of one
 // polynomial, 1024 words per wave (4 waves, or 8 for the wide items of the

@@ -28,7 +28,7 @@
 // The output order uses its own swizzle.
 //
 // The first pass's post-twist P(column, output) is split into a factor fixed
-// per lane (Shoup form, staged in LDS, or read through the caches at 2^14
+// per lane (Shoup form, or in the fusion after a matrix-core level B; staged in LDS, or read through the caches at 2^14
 // where two workgroups' polynomials fill the LDS) and a factor per step
 // (Montgomery form, in registers).
 #include "fourstep_dev.hpp"
