@@ -392,10 +392,10 @@ uint32_t occupancy() {
 template <bool kFirst, int kR, bool kWide, bool kEpi, int kRing>
 uint32_t grid_size(const tfhe_ntt_plan_s* p, uint32_t items) {
   // default: the resident count; for the wide kernels (one resident workgroup
-  // per CU) four times that: the later workgroups are scheduled as the first
-  // drain, which balances the tail (forward and inverse of 44 x 128 at N = 2^16
-  // with 2, 3, 4, 8: 2275, 2287, 2245, 2250 us; HMULT x64 3259, 3267, 3250, 3244)
-  const uint32_t w = p->fs_wg_per_cu ? p->fs_wg_per_cu : kWide ? 4 : occupancy<kFirst, kR, kWide, kEpi, kRing>();
+  // per CU) by the launch's items
+  const uint32_t w = p->fs_wg_per_cu ? p->fs_wg_per_cu
+                     : kWide         ? wide_wg_per_cu(items, p->num_cus)
+                                     : occupancy<kFirst, kR, kWide, kEpi, kRing>();
   const uint32_t g = std::max(16u, (p->num_cus * w) / 16 * 16);
   return std::min(g, (items + 15) / 16 * 16);
 }
