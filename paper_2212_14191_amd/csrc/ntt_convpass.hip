@@ -62,14 +62,15 @@ struct CvTable {
 };
 static_assert(sizeof(CvTable) <= 4096, "a CvTable is passed as a kernel argument");
 
-// Workgroups of 4 waves of 1024 coefficients.  With eight inputs two of them
+// Workgroups of W = 4 waves of 1024 coefficients.  With eight inputs two of them
 // share a CU (256 registers per lane): one's input loads, table copies and
 // barriers run under the other's arithmetic (one 8-wave workgroup per CU took
 // 0.57 instead of 0.54 ms for ModUp of 64 pairs at N = 2^16, level 24).  The
-// plain input leaves room for 16 waves per CU, as two workgroups of 8.
-template <int kR, int kIn>
+// plain input leaves room for 16 waves per CU, as two workgroups of 8 (but see
+// cv_launch_w for small launches).
+template <int kR, int kIn, int W>
 struct CvShape {
-  static constexpr int waves = kIn == 0 && kR > 1 ? 8 : 4, threads = 64 * waves;
+  static constexpr int waves = W, threads = 64 * waves;
   static constexpr int blocks = 4 * kR / waves;  // items per polynomial: N / (1024 waves)
   static constexpr int per_cu = kIn == 8 ? 2 : kIn == 4 ? 3 : 16 / waves;  // workgroups
   // tables of one target in LDS: opA, opB (kR = 16), twist, post_b
@@ -83,10 +84,10 @@ __device__ __forceinline__ int group_of(int m, int t) {
 }
 
 // kIn: inputs held in registers (0: one plane, no conversion).
-template <int kR, int kIn>
-__global__ void __launch_bounds__((CvShape<kR, kIn>::threads), (kIn == 0 && kR > 1 ? 4 : 2))
+template <int kR, int kIn, int W>
+__global__ void __launch_bounds__((CvShape<kR, kIn, W>::threads), (kIn == 0 && kR > 1 ? 4 : 2))
 cv_pass(const CvTable tab) {
-  using S = CvShape<kR, kIn>;
+  using S = CvShape<kR, kIn, W>;
   constexpr int kPlanes = kIn == 0 ? 1 : kIn, Mt = 16 / kR;
   __shared__ __attribute__((aligned(16))) uint32_t lds[1024 * S::waves + 2 * S::tab];
   uint32_t* const tabs = lds + 1024 * S::waves;
@@ -339,9 +340,9 @@ cv_pass(const CvTable tab) {
   }
 }
 
-template <int kR, int kIn>
-hipError_t cv_launch(const tfhe_ntt_plan_s* p, CvTable& t, hipStream_t s) {
-  using S = CvShape<kR, kIn>;
+template <int kR, int kIn, int W>
+hipError_t cv_launch_w(const tfhe_ntt_plan_s* p, CvTable& t, hipStream_t s) {
+  using S = CvShape<kR, kIn, W>;
   // Targets per workgroup: more of them share one load of the inputs, fewer
   // fill the CUs.  Loading the inputs takes about as long as two targets; the
   // workgroups run in rounds of per_cu per CU.
@@ -367,8 +368,27 @@ hipError_t cv_launch(const tfhe_ntt_plan_s* p, CvTable& t, hipStream_t s) {
   if (items >= (1ull << 31)) return hipErrorInvalidValue;
   t.item_begin[t.count] = (uint32_t)items;
   TFHE_TIMED(K_CONV_PASS1, s,
-             hipLaunchKernelGGL((cv_pass<kR, kIn>), dim3((uint32_t)items), dim3(S::threads), 0, s, t));
+             hipLaunchKernelGGL((cv_pass<kR, kIn, W>), dim3((uint32_t)items), dim3(S::threads), 0, s, t));
   return hipGetLastError();
+}
+
+// Without a conversion, workgroups of 8 waves share one copy of the tables among
+// more of them; but at N = 2^13 and 2^14 they took longer to start than the
+// plain first pass that this kernel replaced, and a launch of no more than two
+// 4-wave workgroups per CU is over after one of each (whole RESCALE calls, us, 8
+// waves : 4, N = 2^14: 2 polynomials 22.8 : 21.9, 32 24.3 : 23.1, 128 27.8 :
+// 28.1 / 27.8 : 27.6, 224 32.8 : 34.3, 1472 98 : 101; the pass itself 6.3 : 5.2
+// for 2, plain 5.1; N = 2^13: 32 19.1 : 18.4, 480 46.1 : 48.7; N = 2^15 not
+// clearly either way, 2^16 slower).
+template <int kR, int kIn>
+hipError_t cv_launch(const tfhe_ntt_plan_s* p, CvTable& t, hipStream_t s) {
+  if constexpr (kIn == 0 && (kR == 2 || kR == 4)) {
+    uint64_t items = 0;
+    for (uint32_t k = 0; k < t.count; ++k)
+      items += (uint64_t)t.u[k].targets * t.u[k].batch * CvShape<kR, kIn, 4>::blocks;
+    if (items <= 2ull * p->num_cus) return cv_launch_w<kR, kIn, 4>(p, t, s);
+  }
+  return cv_launch_w<kR, kIn, (kIn == 0 && kR > 1 ? 8 : 4)>(p, t, s);
 }
 
 template <int kIn>
