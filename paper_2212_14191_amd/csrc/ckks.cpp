@@ -73,9 +73,10 @@ static bool fused_inner(const tfhe_ckks_ctx_s* c) {
 
 // Whether inverse transforms that feed a conversion or a broadcast input
 // write quad-tiled results: where their second pass is the two-pass kernel's
-// and natural order would be read in 16- or 32-byte pieces (N >= 2^15).
+// and natural order would be read in 16- or 32-byte pieces (N = 2^15 unless the
+// plan asks for one pass; 2^16, which has two whatever it asks for).
 static bool quad_tiled(const tfhe_ntt_plan_s* p) {
-  return p->algo == TFHE_NTT_FOURSTEP_MFMA && p->log_n >= 15 && p->fs_passes != 1;
+  return p->algo == TFHE_NTT_FOURSTEP_MFMA && (p->log_n == 16 || (p->log_n == 15 && p->fs_passes != 1));
 }
 
 // Workspace of one key-switching batch: its own regions (byte offsets from

@@ -37,3 +37,15 @@ def test_wide_pass_workgroups_keep_their_ring_busy(tmp_path):
         assert w == 1 or items >= 12 * w * cus, (cus, items, w)
         seen.add(w)
     assert seen == {1, 2, 4}
+
+
+def test_inverse_outputs_of_two_pass_transforms_are_quad_tiled(tmp_path):
+    exe = str(tmp_path / "layout")
+    csrc = os.path.join(ROOT, "paper_2212_14191_amd", "csrc")
+    srcs = [os.path.join(csrc, f) for f in ("plan.cpp", "capi.cpp", "ckks.cpp", "timing.cpp")]
+    r = subprocess.run(["g++", "-std=c++17", "-O1", "-I" + os.path.join(SAN, "fakehip"),
+                        "-I" + os.path.join(ROOT, "include"), "-x", "c++"] + srcs
+                       + [os.path.join(SAN, "layout_driver.cpp"), "-lpthread", "-o", exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stdout + r.stderr
