@@ -146,8 +146,12 @@ def _stream(stream=None):
     if stream is not None:
         return ctypes.c_void_p(stream.cuda_stream)
     # the handle of torch.cuda.current_stream(), without building the stream
-    # object (3.0 us of an 8.5 us call at N = 2^12; this takes 0.4)
-    return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    # object (3.0 us of an 8.5 us call at N = 2^12; this takes 0.4) where this
+    # torch has the function that reads it
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return ctypes.c_void_p(raw(torch.cuda.current_device()))
 
 
 # ------------------------------------------------------------ raw entry points
