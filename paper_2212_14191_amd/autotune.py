@@ -120,22 +120,20 @@ def ks_inner_choice(entry):
 def apply_ckks(ctx, table, limbs=24, batch=64, level=24):
     """Tuned plan parameters of a CKKS context's transforms and its key
     switching variant (the inner product fused into the transforms or not).
-    A one-pass choice becomes the library default (fs_passes 0) here: the
-    key switch's plain transforms (the INTT of d2 and of the special limbs)
-    then take one pass for launches with at least two polynomials per CU,
-    which measured 2-8 % faster HMULT at N = 2^12..2^14 and batch 8-64,
-    and two below, where one pass would leave CUs idle (10-20 % slower at
-    batch 1-4).  The persistent grid stays the library's (fs_wg_per_cu 0):
+    The number of passes becomes the library default (fs_passes 0), whose rule
+    follows each launch: the choice was measured for one launch size, while a
+    context's transforms (the INTT of d2 and of the special limbs, plain
+    transforms through its plan) are of many sizes, and either choice is the
+    slower one at some of them (times at use_onepass in csrc/ntt_fourstep.hip).
+    The persistent grid stays the library's (fs_wg_per_cu 0):
     the transform-tuned 4 workgroups per CU measured 0.6-2.4 % slower for
     HMULT at N = 2^15 and 2^16 (levels 12 and 24), whose many launches of
-    other shapes balance better on the resident-count grid.  Returns the
+    other shapes take other grids.  Returns the
     applied entries."""
     e = apply(ctx.plan, table, limbs, batch)
     if e is not None:
         e = dict(e)  # the parameters as applied to this context
-        if e.get("fs_passes") == 1:
-            e["fs_passes"] = 0
-        e["fs_wg_per_cu"] = 0
+        e["fs_passes"] = e["fs_wg_per_cu"] = 0
         for name in ("fs_passes", "fs_wg_per_cu"):
             ctx.plan.set_param(name, e[name])
     h = table.get(hmult_key(ctx.log_n, level))
