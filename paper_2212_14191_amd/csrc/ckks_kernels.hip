@@ -469,7 +469,7 @@ hipError_t ConvQueue::flush(uint32_t num_cus, KernelId id, hipStream_t s) {
 hipError_t launch_frobenius_pair(const uint32_t* in0, uint32_t* out0, const uint32_t* in1, uint32_t* out1,
                                  const GaloisSet& gs, uint32_t rows, uint32_t log_n, hipStream_t s) {
   const uint64_t per = (uint64_t)rows << log_n;
-  if (frob_by_poly(log_n, 2ull * rows)) {
+  if (frob_by_poly(log_n, 2ull * rows, frob_lines(gs, log_n))) {
     frob_switch(log_n, [&](auto ln) {
       constexpr int kLogN = decltype(ln)::value;
       TFHE_TIMED(K_FROB, s, hipLaunchKernelGGL(frobenius_pair_poly<kLogN>, dim3(rows, 2),
@@ -499,12 +499,13 @@ hipError_t launch_tensor_multi(const CtDescSet& set, const ModConst* mods, uint3
 hipError_t launch_frobenius_multi(const CtDescSet& set, uint32_t log_n, hipStream_t s) {
   if (set.count == 0) return hipSuccess;
   uint32_t most = 0;
-  uint64_t polys = 0;
+  uint64_t polys = 0, lines = 0;  // (lines: over the first eight ciphertexts)
   for (uint32_t r = 0; r < set.count; ++r) {
     most = std::max(most, set.c[r].level);
     polys += 2ull * set.c[r].level;
+    if (r < 8) lines += frob_lines(set.c[r].galois, log_n);
   }
-  if (frob_by_poly(log_n, polys)) {
+  if (frob_by_poly(log_n, polys, (uint32_t)(lines / std::min(set.count, 8u)))) {
     frob_switch(log_n, [&](auto ln) {
       constexpr int kLogN = decltype(ln)::value;
       TFHE_TIMED(K_FROB, s, hipLaunchKernelGGL(frobenius_multi_poly<kLogN>, dim3(2 * most, set.count),

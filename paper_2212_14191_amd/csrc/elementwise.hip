@@ -121,7 +121,7 @@ hipError_t load_small_launch(const ModConst* mods, const int32_t* in, uint32_t* 
 
 hipError_t frobenius_launch(const uint32_t* in, uint32_t* out, uint32_t galois, uint32_t rows,
                             uint32_t log_n, hipStream_t s) {
-  if (frob_by_poly(log_n, rows)) {
+  if (frob_by_poly(log_n, rows, frob_lines(galois, log_n))) {
     frob_switch(log_n, [&](auto ln) {
       constexpr int kLogN = decltype(ln)::value;
       TFHE_TIMED(K_FROB, s, hipLaunchKernelGGL(frobenius_poly<kLogN>, dim3(rows), dim3(FrobShape<kLogN>::threads), 0,

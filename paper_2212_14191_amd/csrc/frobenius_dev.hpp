@@ -7,7 +7,8 @@
 // LDS: whole-line loads, gathers whose odd stride hits 64 different banks,
 // whole-line stores.  At N = 2^16 the halves take turns in LDS and a thread
 // keeps its 64 results in registers between.  Bound by HBM for many
-// polynomials (512 at N = 2^16, g = 5 / 5^37: 112 / 190 -> 48 us, 5.6 TB/s).
+// polynomials (512 at N = 2^16, g = 5 / 5^37: 112 / 190 -> 49 us, 5.5 TB/s).
+// Few polynomials leave most CUs idle: frob_by_poly (internal.hpp).
 #pragma once
 #include <type_traits>
 
@@ -15,15 +16,6 @@
 
 namespace tfhe {
 namespace {
-
-// N = 2^12..2^16.  Few polynomials leave most CUs idle and go element by
-// element instead (by polynomial : by element, us, g = 5 / 5^37: 2^13 2.6 :
-// 2.2 / 2.4 (32 polynomials), 2.7 : 2.5 / 3.0 (64); 2^14 3.0 : 2.5 / 3.5 (32),
-// 3.3 : 3.1 / 6.7 (64); 2^15 3.8 : 2.5 / 3.9 (16), 4.0 : 3.1 / 7.4 (32); 2^16
-// 9.3 : 3.1 / 7.5 (16), 9.9 : 9.4 / 13.4 (32)).
-inline bool frob_by_poly(uint32_t log_n, uint64_t polys) {
-  return log_n >= 12 && log_n <= 16 && polys >= (log_n >= 15 ? 32 : 64);
-}
 
 template <int kLogN>
 struct FrobShape {

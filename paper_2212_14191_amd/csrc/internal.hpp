@@ -228,6 +228,56 @@ struct GaloisSet {
   uint32_t batch;
   uint32_t g[kMaxRotBatch];
 };
+// How many lines (of 128 bytes) 64 lanes touch that map a polynomial element by
+// element: 2-3 for the identity and the conjugation, 2 |g| for small g, 64 at
+// most.  g = +-1 mod N / k (rotations by N / 4k slots and their multiples) is k
+// streams; what a lane leaves of a line is read N / k elements on, for k <= 16
+// and N >= 2^15 by a workgroup of the same XCD, so they count less (times below).
+inline uint32_t frob_lines(uint32_t galois, uint32_t log_n) {
+  uint64_t seen[32] = {};  // N <= 2^16
+  uint32_t src = galois / 2, lines = 0;
+  for (uint32_t j = 0; j < 64; ++j, src += galois) {
+    const uint32_t line = (src & ((1u << log_n) - 1)) / 32;
+    const uint64_t bit = 1ull << (line % 64);
+    lines += (seen[line / 64] & bit) == 0;
+    seen[line / 64] |= bit;
+  }
+  const uint32_t part = (1u << log_n) / 16 - 1;
+  const bool streams = (galois & part) == 1 || (galois & part) == part;
+  return log_n < 15 || !streams ? lines : log_n == 15 ? lines / 2 : lines / 4;
+}
+// Whether FrobeniusMap goes by whole polynomials through LDS (frobenius_dev.hpp,
+// N = 2^12..2^16) or element by element: the former once there are enough
+// polynomials to fill the CUs, the earlier the more lines the latter touches.
+// With g = +-1 that reads whole lines itself, and at N >= 2^15, where a workgroup
+// fills a CU's LDS, stays ahead until input and output outgrow the last-level
+// cache.  us, by element : by polynomial, `polys` at galois -1, 3, 5, 25 / 5^37:
+//   2^12  96    2.8:2.8   2.8:2.8   2.8:2.9   3.1:2.9 /  3.0:2.9;  192  3.2:3.0   3.2:3.0   3.2:3.0    4.0:3.0
+//   2^13  64    2.9:3.1   2.9:3.1   2.9:3.1   3.9:3.1 /  3.4:3.1;  128  3.5:3.4   3.5:3.4   3.5:3.4    6.5:3.4
+//   2^14  64    3.5:3.7   3.5:3.7   3.5:3.6   6.5:3.7 /  7.0:3.7;  96   4.1:4.0   4.0:4.0   5.9:4.0    9.7:4.0
+//         256   6.0:5.6-7.1 11.6:5.6 15.6:5.6 21.5:5.6;           384  10.0:8.3 16.1:8.7  21.5:8.7   31.4:8.7
+//   2^15  32    3.5:4.4   3.5:4.4   3.6:4.4   6.5:4.4 /  7.7:4.4;  48   4.1:4.7   4.0:4.7   5.9:4.7    9.7:4.8
+//         96    5.3:6.2   9.6:6.2  12.4:6.2  16.7:6.2;             1024 40:43     73:43     112:43     175:43
+//   2^16  32    4.8:10.2  4.9:10.2  9.6:10.3 12.0:10.2 / 13.7:10.2; 48  5.3:11.0  9.5:11.0 12.4:11.0  16.8:11.0
+//         64    6.0:11.9 11.4:11.9 15.6:11.9 21.6:11.8;            96  10.3:14.3 16.1:14.2 21.5:14.2  31.4:14.2
+//         512   40:49     73:49     112:49    176:49;             1024 122:111   144:111   232:111    497:110
+// and at galois 1 + N / 4, 1 + N / 8, 1 + N / 16:
+//   2^15  48    4.1:4.7   4.6:4.7    6.0:4.7;  96  5.6:6.1   6.8:6.1   9.6:6.1;   512  21.7:22.7  26:23  41:23
+//   2^16  48    5.5:11    6.6:11.0   9.2:11.0; 96  10.3:14   12.5:14   17.5:14.1; 512  39:49      50:49  81:49
+inline bool frob_by_poly(uint32_t log_n, uint64_t polys, uint32_t lines) {
+  if (log_n < 12 || log_n > 16) return false;
+  if (lines <= 4) return log_n >= 15 ? polys << log_n > 1ull << 25 : polys >= (log_n == 14 ? 384 : 192);
+  if (lines <= 8) return polys >= 96;
+  if (lines <= 32) return polys >= (log_n >= 15 ? 48 : 96);
+  return polys >= (log_n >= 15 ? 32 : 64);
+}
+// The same for a set: the mean over the first eight.
+inline uint32_t frob_lines(const GaloisSet& gs, uint32_t log_n) {
+  const uint32_t n = gs.batch < 8 ? gs.batch : 8;
+  uint32_t sum = 0;
+  for (uint32_t b = 0; b < n; ++b) sum += frob_lines(gs.g[b], log_n);
+  return sum / n;
+}
 
 // ---- per-kernel event timing (timing.cpp)
 enum KernelId {
