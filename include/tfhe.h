@@ -109,8 +109,8 @@ tfhe_status tfhe_ntt_plan_modulus(tfhe_ntt_plan plan, uint32_t limb, uint32_t* q
 /* Tuning knobs of a plan (written by an autotuner; the defaults are sound):
  *   TFHE_PARAM_FS_WG_PER_CU  persistent four-step workgroups per compute
  *                            unit (0 = library default: as many as fit;
- *                            passes with 8-wave items one, two or four by
- *                            the launch's items per compute unit)
+ *                            passes with 8-wave items one to five by the
+ *                            launch's items per compute unit)
  *   TFHE_PARAM_AUTO_ALGO     what TFHE_NTT_AUTO resolves to (a tfhe_ntt_algo;
  *                            MFMA only where the plan supports it)
  *   TFHE_PARAM_FS_WIDE       work items of the four-step 256-point stage:

@@ -194,18 +194,29 @@ hipError_t fs_inverse(const tfhe_ntt_plan_s* p, const uint32_t* in, uint32_t* ou
 // fills its ring and loads its limb's tables (first pass: 64 KiB of post-twist
 // among them) anew, and with one item each it prefetches nothing, so a launch of
 // few items takes one workgroup per CU; with many, several balance the tail.
-// Forward = inverse within 1 %, us with 1 : 2 : 4 per CU, by items per CU:
-//   N = 2^16  3  27.4 : 35.1 : 34.2;  4  35.9 : 37.9 : 45.3;  6  47.2 : 52.0 : 66.7;
-//             10  70.9 : 75.0 : 90.7;  20  132.9 : 134.0 : 139.7;  24  162.3 : 159.5 : 163.0;
-//             32 (44 x 23)  225 : 213 : 225;  40  274 : 258 : 258;  64  410 : 434 : 441;
-//             96  618 : 610 : 627;  176  1146 : 1123 : 1100
-//   N = 2^15  3  31.1 : 35.7 : 34.4;  6  49.3 : 51.3 : 60.9;  12  85.6 : 87.6 : 91.5;
-//             24  160 : 162 : 167;  44  301 : 292 : 298;  64  425 : 426 : 418
-//   RESCALE, N = 2^16, level 24, 2..64 elements: 41.4 : 47.1 : 43.2, 62.5 : 63.1 : 74.3,
-//             102 : 103 : 106, 180 : 185 : 189, 371 : 377 : 380, 713 : 722 : 725
+// Every 16 workgroups walk a range of polynomials of their own; where these
+// ranges start a multiple of 16 polynomials apart, all walk the same addresses
+// modulo some MiB, and five (other ranges) are faster than four.
+// us with 1 : 2 : 4 (: 5) per CU, by items per CU:
+//   N = 2^16, one direction
+//      3  27.4 : 35.1 : 34.2;   4  35.9 : 37.9 : 45.3;   6  47.2 : 52.0 : 66.7;
+//     10  70.9 : 75.0 : 90.7;  20  132.9 : 134.0 : 139.7;  24  162.3 : 159.5 : 163.0
+//   N = 2^16, forward and inverse
+//     28  371 : 383 : 383 : 392;   38  509 : 505 : 509 : 529;  40 (8 limbs)  542 : 530 : 516 : 561;
+//     48  662 : 653 : 623 : 631;   60  807 : 789 : 777 : 781;  104  1394 : 1359 : 1337 : 1349;
+//    176  2305 : 2274 : 2247 : 2262;  16 n polynomials apart (with four):  64  834 : 882 : 886 : 835;
+//     96  1257 : 1241 : 1258 : 1236;  128  1688 : 1719 : 1816 : 1651
+//   N = 2^15, forward and inverse
+//     16  234 : 242 : 246 : 259;   48  647 : 645 : 646 : 653;  88  1164 : 1156 : 1154 : 1164
+//   RESCALE, N = 2^16, level 24, 2..32 elements (1 : 2 : 4): 41.4 : 47.1 : 43.2, 62.5 : 63.1 : 74.3,
+//     102 : 103 : 106, 180 : 185 : 189, 371 : 377 : 380
 //   HMULT, N = 2^16, level 12, 4 pairs: 139.8 : 153.1 : 149.6, 8: 239 : 250 : 273, 64: 1656 : 1640 : 1646
-inline uint32_t wide_wg_per_cu(uint64_t items, uint32_t num_cus) {
-  return items <= 24ull * num_cus ? 1 : items < 128ull * num_cus ? 2 : 4;
+inline uint32_t wide_wg_per_cu(uint32_t polys, uint32_t items_per_poly, uint32_t num_cus) {
+  const uint64_t items = (uint64_t)polys * items_per_poly;
+  if (items <= 24ull * num_cus) return 1;
+  if (items < 48ull * num_cus) return 2;
+  const uint32_t groups = num_cus * 4 / 16, apart = (polys + groups / 2) / groups;
+  return apart % 16 == 0 ? 5 : 4;
 }
 // Vector-ALU GEMM variant of the same passes (plan->has_co); same workspace.
 hipError_t co_transform(const tfhe_ntt_plan_s* p, bool inverse, const uint32_t* in, uint32_t* out,

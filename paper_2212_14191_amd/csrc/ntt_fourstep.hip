@@ -390,14 +390,14 @@ uint32_t occupancy() {
 
 // Persistent grid: a multiple of 16 workgroups, no more than the items need.
 template <bool kFirst, int kR, bool kWide, bool kEpi, int kRing>
-uint32_t grid_size(const tfhe_ntt_plan_s* p, uint32_t items) {
+uint32_t grid_size(const tfhe_ntt_plan_s* p, uint32_t polys, uint32_t ipp_log) {
   // default: the resident count; for the wide kernels (one resident workgroup
   // per CU) by the launch's items
   const uint32_t w = p->fs_wg_per_cu ? p->fs_wg_per_cu
-                     : kWide         ? wide_wg_per_cu(items, p->num_cus)
+                     : kWide         ? wide_wg_per_cu(polys, 1u << ipp_log, p->num_cus)
                                      : occupancy<kFirst, kR, kWide, kEpi, kRing>();
   const uint32_t g = std::max(16u, (p->num_cus * w) / 16 * 16);
-  return std::min(g, (items + 15) / 16 * 16);
+  return std::min(g, ((polys << ipp_log) + 15) / 16 * 16);
 }
 
 // Each of `groups` walkers' number of polynomials; the first `extra` take one more.
@@ -410,7 +410,7 @@ template <bool kFirst, int kR, bool kWide, bool kEpi, int kRing>
 void launch_ring(const tfhe_ntt_plan_s* p, FsTable t, hipStream_t s) {
   using G = Geo<kFirst, kR, kWide>;
   t.ipp_log = t.log_n - (kWide ? 13 : 12);  // items per polynomial: N / item words
-  const uint32_t grid = grid_size<kFirst, kR, kWide, kEpi, kRing>(p, t.total << t.ipp_log);
+  const uint32_t grid = grid_size<kFirst, kR, kWide, kEpi, kRing>(p, t.total, t.ipp_log);
   share_out(t, grid / 16);
   TFHE_TIMED(kFirst ? K_FS_PASS1 : K_FS_PASS2, s,
              hipLaunchKernelGGL((fs_pass<kFirst, kR, kWide, kEpi, kRing>), dim3(grid), dim3(G::threads), 0, s, t));
