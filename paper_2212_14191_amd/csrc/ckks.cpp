@@ -108,6 +108,10 @@ static KsLayout ks_layout(const tfhe_ckks_ctx_s* c, uint32_t level, uint32_t bat
     const uint32_t d0 = c->alpha * j, nd = std::min(c->alpha, level - d0);
     modup += ws(d0) + ws(level - d0 - nd) + ws(c->K);
   }
+  // Four-step plans convert inside the transforms: with the fused inner product
+  // they leave `up` untouched, and `conv` always.  Both stay reserved, so that a
+  // workspace sized once serves every inner product and algorithm that the plan
+  // is later set to, and a batch that tfhe_hmult_noalloc refuses stays refused.
   KsLayout l;
   // with the fused second pass + inner product, the ModUp transforms'
   // intermediates sit in a regular [digits][level + K] array of planes

@@ -20,9 +20,9 @@ __device__ __forceinline__ uint4 ew(uint4 x, uint4 y, const ModConst& m) {
 // blockIdx.y is the limb, so that its constants are scalar (an index over all
 // limbs took a 64-bit division per 16 bytes).  A ciphertext op does both
 // components of a position: one launch, and CMULT reads its plaintext once.
-// Bound by HBM; CMULT then HADD of 32 ciphertexts, N = 2^15, level 12: 99 ->
-// 88 us (6.2 TB/s, part of it the last-level cache's).  Streaming hints on the
-// loads or stores are slower (89-92 us).
+// Bound by HBM; CMULT then HADD of 32 ciphertexts, N = 2^15, level 12: 103 ->
+// 97 us for the pair of calls (554 MB; 5.7 TB/s, part of it the last-level
+// cache's).  Streaming hints on the loads or stores are 1-4 % slower.
 template <int kOp>
 __global__ void __launch_bounds__(kThreads)
 ew_kernel(const ModConst* __restrict__ mods, const uint4* __restrict__ a, const uint4* __restrict__ b,
