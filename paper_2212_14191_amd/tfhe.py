@@ -148,8 +148,9 @@ def _stream(stream=None):
     # the handle of torch.cuda.current_stream(), without building the stream
     # object (3.0 us of an 8.5 us call at N = 2^12; this takes 0.4) where this
     # torch has the function that reads it
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    if raw is None:
+    try:
+        raw = torch._C._cuda_getCurrentRawStream
+    except AttributeError:
         return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
     return ctypes.c_void_p(raw(torch.cuda.current_device()))
 
