@@ -215,7 +215,7 @@ inline uint32_t wide_wg_per_cu(uint32_t polys, uint32_t items_per_poly, uint32_t
   const uint64_t items = (uint64_t)polys * items_per_poly;
   if (items <= 24ull * num_cus) return 1;
   if (items < 48ull * num_cus) return 2;
-  const uint32_t groups = num_cus * 4 / 16, apart = (polys + groups / 2) / groups;
+  const uint32_t groups = num_cus >= 4 ? num_cus / 4 : 1, apart = (polys + groups / 2) / groups;
   return apart % 16 == 0 ? 5 : 4;
 }
 // Vector-ALU GEMM variant of the same passes (plan->has_co); same workspace.

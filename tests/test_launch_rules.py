@@ -15,7 +15,7 @@ DRIVER = """
 #include <cstdio>
 #include "../paper_2212_14191_amd/csrc/internal.hpp"
 int main() {
-  for (uint32_t cus : {32u, 256u, 304u})
+  for (uint32_t cus : {1u, 32u, 256u, 304u})
     for (uint32_t ipp : {1u, 4u, 8u})
       for (uint32_t polys = 1; polys * ipp <= 200 * cus; polys += polys * ipp < 60 * cus ? 1 : 7)
         std::printf("%u %u %u\\n", cus, polys * ipp, tfhe::wide_wg_per_cu(polys, ipp, cus));
